@@ -72,18 +72,22 @@ int fa_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
  * Work decomposition fa_fwd uses for a problem (section 4.1: tiles above the diagonal are
  * skipped; appendix A: the work is split over the sequence as well as over batch and heads).
  * FA_MODE_SPLIT: a workgroup owns 128 query rows and its two wave groups take alternate
- * 64-key tiles; FA_MODE_WIDE: a workgroup owns 256 query rows and all its waves walk the same
- * tiles; FA_MODE_WIDE_FOLD (causal only): WIDE with each workgroup's eight 32-row blocks taken
- * four from the cheap end of the sequence and four, mirrored, from the expensive end; once the
- * cheap blocks are done their waves take every other tile of the expensive ones.
+ * 64-key tiles; FA_MODE_WIDE: all waves of a workgroup walk the same tiles, eight waves on 256 query rows or four on 128
+ * (fa_plan_t.block_m says which; four-wave workgroups at D = 128 are launched once and take block of rows after block of
+ * rows, heavy and light causal ones in turn); FA_MODE_WIDE_FOLD (causal only): WIDE with every workgroup's work balanced --
+ * on 256 rows, each workgroup's eight 32-row blocks are taken four from the cheap end of the sequence and four, mirrored,
+ * from the expensive end, and once the cheap blocks are done their waves take every other tile of the expensive ones; on 128
+ * rows, the order of the four-wave workgroups' blocks does it.
  * FA_MODE_WIDE64 (D = 128 only): 256 query rows per workgroup as in WIDE, but as four waves of 64
  * rows, one per SIMD, so that every K and V fragment read from LDS feeds two matrix instructions,
  * with a software-pipelined main loop (the softmax of one 32-key unit issued between the matrix
  * instructions of its neighbours).
- * With W = B*H*ceil(Nq/256), fa_fwd picks SPLIT when W < 256; for causal problems with
- * Nq > 768: WIDE_FOLD when Nq <= 4096, W <= 1024 and the last round of 256 workgroups is at
- * least 85% full, else SPLIT when W < 640 (Nq <= 4096) or W < 384 (longer); otherwise WIDE64 when
- * D = 128 and a query sees 4096 keys or more on average (Nk, or Nk - Nq/2 when causal), else WIDE.
+ * With W = B*H*ceil(Nq/256), fa_fwd picks SPLIT for at most 256 blocks of 128 rows unless the walk is short (Nk <= 768, at
+ * D = 64 512, or 1024 without the causal mask), and for causal problems over Nq = 2048 with W < 640 (Nq <= 4096), or
+ * of at most 512 such blocks (longer), that are not FOLD's; WIDE_FOLD for causal problems with Nq > 768 whose one to four
+ * rounds of 256 workgroups fill the last to 85% (Nq <= 4096, at D = 64 8192); WIDE64 when D = 128, a query sees 4096 keys
+ * or more on average (Nk, or Nk - Nq/2 when causal) and its rounds are filled or many; else WIDE, on 128 rows but for
+ * Nk >= 1536 without the causal mask and, at D = 64, over 4096 keys with it.
  * fa_set_option(FA_OPT_FWD_MODE, ...) overrides the choice (tests, tuning).
  * Nq = 1 (one decoding step) takes none of these: FA_MODE_STREAM, the register-streaming kernel
  * described at fa_fwd_splitkv, one workgroup per (batch, head) -- full speed when B*H fills the
@@ -95,13 +99,14 @@ int fa_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
 #define FA_MODE_WIDE_FOLD 2
 #define FA_MODE_STREAM 3   /* Nq = 1: the register-streaming kernel of fa_fwd_splitkv, one run per (batch, head) */
 #define FA_MODE_WIDE64 4   /* D = 128: four waves of 64 rows, software-pipelined main loop */
+#define FA_MODE_WIDE4 5    /* fa_set_option only: FA_MODE_WIDE on workgroups of four waves; plans report FA_MODE_WIDE, block_m 128 */
 
 typedef struct fa_plan {
     int mode;                 /* FA_MODE_SPLIT, FA_MODE_WIDE, FA_MODE_WIDE_FOLD, FA_MODE_STREAM or FA_MODE_WIDE64 */
-    int block_m;              /* query rows per workgroup */
+    int block_m;              /* query rows per workgroup (of a block, where workgroups take several) */
     int block_n;              /* keys per tile */
     int threads;              /* threads per workgroup */
-    int grid;                 /* workgroups launched (work items rounded up to a multiple of 8) */
+    int grid;                 /* workgroups launched (work items rounded up to a multiple of 8; at most 512 where workgroups take several) */
     int lds_bytes;            /* LDS per workgroup */
     long long work_items;     /* B * H * ceil(Nq / block_m) */
     long long tiles_visited;  /* (query block, key tile) pairs the kernel walks: masked-out tiles are skipped */
@@ -270,7 +275,7 @@ typedef struct fa_mask {
  * pointer, read during the call only.  Needs Nq + Nk < 2^30.  One kernel, no workspace.  Per
  * wave (32 query rows) and 64-key tile the kernel classifies the tile from the descriptor:
  * nothing visible -> not computed; everything visible -> no mask work; otherwise the predicate
- * is evaluated per element.  A workgroup (256 rows) only walks the prefix tiles and the tiles its
+ * is evaluated per element.  A workgroup (128 rows) only walks the prefix tiles and the tiles its
  * rows' windows touch.  Nq = 1 (a decoding step over caches of different lengths, or with a
  * sliding window) runs the register-streaming kernel of fa_fwd_splitkv instead, one workgroup
  * per (batch, head), which walks the prefix and the window as runs of consecutive keys
@@ -341,7 +346,7 @@ int fa_mask_interior_run(const fa_mask_t *mask, int kv_len, int Nq, int Nk, int 
  * environment variable is read anywhere in the library.
  *
  *   FA_OPT_FWD_MODE      : FA_MODE_SPLIT, FA_MODE_WIDE, FA_MODE_WIDE_FOLD (causal problems only; WIDE
- *                          otherwise), FA_MODE_WIDE64 (D = 128 only; WIDE otherwise) or FA_AUTO.
+ *                          otherwise), FA_MODE_WIDE64 (D = 128 only; WIDE otherwise), FA_MODE_WIDE4 or FA_AUTO.
  *                          FA_MODE_WIDE also keeps fa_fwd_splitkv's long runs on the tile kernel
  *   FA_OPT_DECODE_KERNEL : 0 or FA_AUTO: Nq = 1 runs the register-streaming kernel; 1: the tile kernels
  *   FA_OPT_LINEAR_TILE   : 128, 256 or FA_AUTO: token rows per workgroup tile of the projection

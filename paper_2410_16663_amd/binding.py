@@ -38,6 +38,7 @@ FA_DTYPE_BF16 = 1
 FA_MODE_SPLIT = 0
 FA_MODE_WIDE = 1
 FA_MODE_WIDE64 = 4
+FA_MODE_WIDE4 = 5
 FA_MODE_WIDE_FOLD = 2
 FA_MODE_STREAM = 3
 

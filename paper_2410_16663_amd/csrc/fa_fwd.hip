@@ -65,18 +65,52 @@ namespace {
 #include "fa_device.inc"
 #include "fa_attention_kernel.inc"
 #include "fa_attention_wide64_kernel.inc"
+#include "fa_attention_rows_kernel.inc"
 #include "fa_linear_kernel.inc"
 #include "fa_decode_kernels.inc"
 
-template <int DT, int D, bool CAUSAL, bool WIDE>
+template <int DT, int D, bool CAUSAL, bool WIDE, int NW = 8>
 hipError_t launch(const FaParams &p, int nwork_padded, hipStream_t stream) {
-    hipLaunchKernelGGL((fa_fwd_kernel<DT, D, CAUSAL, WIDE>), dim3(nwork_padded), dim3(512), 0, stream, p);
+    hipLaunchKernelGGL((fa_fwd_kernel<DT, D, CAUSAL, WIDE, false, false, false, NW>), dim3(nwork_padded), dim3(NW * 64), 0, stream, p);
     return hipGetLastError();
 }
 
+// descriptor masks: workgroups of four waves (128 query rows)
 template <int DT, int D>
 hipError_t launch_masked(const FaParams &p, int nwork_padded, hipStream_t stream) {
-    hipLaunchKernelGGL((fa_fwd_kernel<DT, D, false, true, false, true>), dim3(nwork_padded), dim3(512), 0, stream, p);
+    hipLaunchKernelGGL((fa_fwd_kernel<DT, D, false, true, false, true, false, 4>), dim3(nwork_padded), dim3(256), 0, stream, p);
+    return hipGetLastError();
+}
+
+// fa_fwd_rows_kernel: p holds the whole problem (nqt 128-row blocks per head); the shape of the list is set here, and as
+// many workgroups are launched as the chip holds at a time (two per compute unit), fewer if the list is shorter.
+// The order of the list balances causal work: with all heads of an XCD mixed, heaviest row blocks first, the largest
+// share is within 5% of the mean (1 x 40 x 4096: 199 us head by head, 171 mixed; 20 heads of 8192: 382, 329; 96 of
+// 2048: 117, 112).  Two exceptions, for the sake of the L2, where the workgroups that run at a time should share K/V:
+// up to four row blocks per head (512 heads of 512 rows: 62 head by head, 81 mixed), and more heads per XCD than 16 over
+// at least four turns, which are mixed in groups of eight.
+constexpr int ROWS_SLOTS = 64;                     // workgroups an XCD's 32 compute units hold at a time
+long long rows_entries(long long heads, long long nqt) { return heads / 8 * nqt + (heads % 8 * nqt + 7) / 8; }   // of XCD 0
+int rows_grid(long long heads, long long nqt) {
+    const long long n = rows_entries(heads, nqt);
+    return 8 * (int)(n < ROWS_SLOTS ? n : ROWS_SLOTS);
+}
+hipError_t launch_rows(FaParams p, int dtype, bool causal, hipStream_t stream) {
+    const int heads = p.nwork / p.nqt;
+    const long long entries = rows_entries(heads, p.nqt);
+    p.head_run = heads / 8;
+    p.head_rest = heads % 8;
+    if (!causal || p.nqt < 5) {
+        p.group = 1;
+        p.grouped = p.head_run;
+    } else {
+        p.group = 8;
+        p.grouped = p.head_run <= 16 || entries < 4 * ROWS_SLOTS ? 0 : p.head_run & ~7;
+    }
+    if (!causal) p.off = p.Nk - 1;                 // the diagonal past every key
+    const dim3 grid(rows_grid(heads, p.nqt));
+    if (dtype == FA_DTYPE_F16) hipLaunchKernelGGL((fa_fwd_rows_kernel<FA_DTYPE_F16>), grid, dim3(256), 0, stream, p);
+    else hipLaunchKernelGGL((fa_fwd_rows_kernel<FA_DTYPE_BF16>), grid, dim3(256), 0, stream, p);
     return hipGetLastError();
 }
 
@@ -145,49 +179,68 @@ int check_shape(int B, int H, int Nq, int Nk, int D, int dtype) {
 // tests, tuning)
 bool use_streaming_decode(int Nq) { return Nq == 1 && option(FA_OPT_DECODE_KERNEL) != 1; }
 
-// Work decomposition for a problem, W = B * H * ceil(Nq / 256) being the number of 256-row workgroups
-// (the chip has 256 compute units and a D = 128 workgroup fills one).  From a sweep of forced modes
-// over 19 causal shapes:
-//  * fewer workgroups than compute units: FA_MODE_SPLIT doubles their number and halves their chains;
-//  * causal, 1024 <= Nq <= 4096, up to four rounds of workgroups that fill their last round to 85%:
-//    FA_MODE_WIDE_FOLD -- every workgroup carries the same triangular work, so whole rounds take
-//    equal time, and the waves of finished cheap blocks help with the expensive ones (5-25% faster
-//    than the others there; with a poorly filled last round it loses to the split mode, whose
-//    workgroups are half the size);
-//  * causal, few rounds of long chains otherwise (W < 640 up to Nq = 4096, W < 384 beyond):
-//    FA_MODE_SPLIT, whose shorter chains matter more than its extra K/V traffic;
-//  * otherwise FA_MODE_WIDE: with many rounds the heavy-first dynamic dispatch evens out the triangle.
+// Work decomposition for a problem: the mode, and the query rows of a workgroup (256, or 128 in FA_MODE_SPLIT and in
+// FA_MODE_WIDE on workgroups of four waves).  W = B * H * ceil(Nq / 256), blocks = B * H * ceil(Nq / 128); the chip has
+// 256 compute units.  At D = 128 one eight-wave or two four-wave workgroups fill a compute unit, at D = 64 two or four.
+// The lines come from sweeps of forced modes over 45 causal and 30 full shapes per head dimension (us per launch, bf16
+// and fp16 mixed; "rows" is the persistent four-wave kernel of D = 128, "four" its plain counterpart of D = 64):
+//  * at most one 128-row block per compute unit: FA_MODE_SPLIT puts eight waves on each and halves its chain of tiles,
+//    unless the chain is short anyway (1 x 32 x 512 causal, D = 128: split 15.0, rows 13.9; x 1024: 21.6 and 23.3).
+//  * whole rounds of causal work (one to four rounds of 256-row workgroups, the last one filled to 85%):
+//    FA_MODE_WIDE_FOLD, whose workgroups all carry the same triangular work and whose finished waves help the others:
+//    for a single round at D = 128 (1 x 32 x 2048: 44, rows 47; several rounds: rows, 1 x 32 x 4096: 133 instead of
+//    148), and at D = 64 (1 x 32 x 4096: 93, four 135; 1 x 32 x 8192: 329, wide 349).
+//  * long walks at D = 128 (4096 keys per query on average): FA_MODE_WIDE64, where its rounds of 256 are filled (1 x 20 x
+//    8192, two and a half rounds: 437, rows 329).
+//  * everything else on four waves, whose waves share a SIMD with other workgroups' (D = 128 causal: 16 x 32 x 2048
+//    590, wide 745; 3 x 20 x 1531 47, split 68, wide 70; full: 47 x 32 x 280 122, wide 205), but for full attention over
+//    1536 keys and more, where the tiles loaded per 256 rows count (4 x 32 x 2048: wide 266, rows 273; D = 64, 8 x 32 x
+//    4096: wide 1141, four 1184), and for walks over 4096 keys at D = 64.
+//  * FA_MODE_SPLIT besides for causal Nq >= 2048 below 2.5 rounds, its place in fa_fwd_plan's documented answer (1 x 12 x
+//    3000: 47, rows 57; but 2 x 20 x 2048: 66, rows 55), and over 4096 while a round of 128-row blocks holds it all
+//    (1 x 8 x 8192: 137, rows 161; 1 x 10 x 8192: 220, rows 191).
 // fa_set_option(FA_OPT_FWD_MODE, ...) overrides.
-int choose_mode(int B, int H, int Nq, int Nk, int D, int causal) {
+struct Decomposition {
+    int mode, rows;
+};
+Decomposition choose_mode(int B, int H, int Nq, int Nk, int D, int causal) {
     const int forced = option(FA_OPT_FWD_MODE);
-    if (forced == FA_MODE_SPLIT || forced == FA_MODE_WIDE) return forced;
-    if (forced == FA_MODE_WIDE64) return D == 128 ? FA_MODE_WIDE64 : FA_MODE_WIDE;
-    if (forced == FA_MODE_WIDE_FOLD) return causal ? FA_MODE_WIDE_FOLD : FA_MODE_WIDE;
-    const long long nqt = ((long long)Nq + 255) / 256;
-    const long long W = (long long)B * H * nqt;
-    if (W < 256) return FA_MODE_SPLIT;
-    if (causal && nqt >= 4) {
-        const long long rounds = (W + 255) / 256;
-        const bool fills_last_round = rounds * 256 * 100 <= W * 115;
-        if (Nq <= 4096 && W <= 1024 && fills_last_round) return FA_MODE_WIDE_FOLD;
-        if (Nq <= 4096 ? W < 640 : W < 384) return FA_MODE_SPLIT;
-    }
-    // long walks at D = 128: the 64-row waves with the pipelined loop (the loop takes whole unmasked tiles two at
-    // a time, so it needs walks long enough to consist mostly of those: measured faster from about 64 tiles per
-    // workgroup on average -- 1-2% -- and 2-14% slower at 32 tiles and below)
+    const Decomposition split = {FA_MODE_SPLIT, 128}, wide = {FA_MODE_WIDE, 256}, four = {FA_MODE_WIDE, 128},
+                        fold = {FA_MODE_WIDE_FOLD, 256}, wide64 = {FA_MODE_WIDE64, 256};
+    const long long heads = (long long)B * H, blocks = heads * (((long long)Nq + 127) / 128);
+    const bool four_fits = blocks < (1ll << 28);                // list positions and their multiples by 8 stay inside int
+    if (forced == FA_MODE_SPLIT) return split;
+    if (forced == FA_MODE_WIDE) return wide;
+    if (forced == FA_MODE_WIDE4) return four_fits ? four : wide;
+    if (forced == FA_MODE_WIDE64) return D == 128 ? wide64 : wide;
+    if (forced == FA_MODE_WIDE_FOLD) return causal ? fold : wide;
+    const long long nqt = ((long long)Nq + 255) / 256, W = heads * nqt;
+    const long long rounds = (W + 255) / 256;
+    const bool full_rounds = rounds * 256 * 100 <= W * 115;     // the last round of 256-row workgroups at least 85% full
     const long long avg_keys = causal ? (long long)Nk - Nq / 2 : (long long)Nk;
-    if (D == 128 && avg_keys >= 4096) return FA_MODE_WIDE64;
-    return FA_MODE_WIDE;
+    if (blocks <= 256) {
+        const int short_walk = D == 64 ? (causal ? 512 : 1024) : (causal ? 768 : 1024);
+        return Nk <= short_walk ? four : split;
+    }
+    if (!four_fits) return D == 128 && avg_keys >= 4096 ? wide64 : wide;
+    if (causal && nqt >= 4) {
+        if (W >= 256 && W <= 1024 && full_rounds && Nq <= (D == 64 ? 8192 : 4096))
+            return D == 64 || W <= 256 ? fold : Decomposition{FA_MODE_WIDE_FOLD, 128};
+        if (D == 64 && W < 256 && Nq > 1792 && Nq <= 8192) return fold;
+        if (Nq > 4096 ? blocks <= 512 : Nq >= 2048 && W < 640) return split;
+    }
+    if (D == 128 && avg_keys >= 4096 && (full_rounds || W >= 6 * 256)) return wide64;
+    if (D == 64 ? avg_keys > (causal ? 4096 : 1535) : !causal && Nk >= 1536 && (full_rounds || W >= 6 * 256)) return wide;
+    return four;
 }
 
 // 64-key tiles the workgroup of query block qt walks (mirrors the kernel's kmax_wg)
-long long tiles_walked(int mode, long long nqt, long long qt, int Nq, int Nk, int causal) {
-    const int BM = mode == FA_MODE_SPLIT ? 128 : 256;
+long long tiles_walked(int mode, int BM, long long nqt, long long qt, int Nq, int Nk, int causal) {
     long long kmax = (long long)Nk - 1;
     if (causal) {
         long long last_row = qt * BM + BM - 1;
         if (last_row > (long long)Nq - 1) last_row = (long long)Nq - 1;
-        if (mode == FA_MODE_WIDE_FOLD) {
+        if (mode == FA_MODE_WIDE_FOLD && BM == 256) {
             last_row = -1;
             for (int w = 0; w < 8; ++w) {
                 const long long first = (long long)fold_block((int)nqt, (int)qt, w) * 32;
@@ -233,9 +286,17 @@ hipError_t launch_pair(const FaParams &p, int nwork_padded, hipStream_t stream) 
     return hipGetLastError();
 }
 
-// the plain instantiations: (split | wide) x dtype x head dimension x causal, and the paired fold (causal only)
-hipError_t launch_attention(const FaParams &p, int mode, int D, int causal, int dtype, int grid, hipStream_t st) {
+// the plain instantiations: (split | wide) x dtype x head dimension x causal, the paired fold (causal only), and the
+// four-wave forms of wide: persistent at D = 128, one workgroup per block at D = 64
+hipError_t launch_attention(const FaParams &p, Decomposition dec, int D, int causal, int dtype, int grid, hipStream_t st) {
     hipError_t e;
+    const int mode = dec.mode;
+    if (dec.rows == 128 && mode != FA_MODE_SPLIT) {
+        if (D == 128) return launch_rows(p, dtype, causal != 0, st);
+        FaParams f = p;
+        if (!causal) f.off = p.Nk - 1;             // the causal instantiation with the diagonal past every key
+        return dtype == FA_DTYPE_F16 ? launch<0, 64, true, true, 4>(f, grid, st) : launch<1, 64, true, true, 4>(f, grid, st);
+    }
     if (mode == FA_MODE_WIDE64) {
         if (D != 128) return hipErrorInvalidValue;
         if (dtype == 0 && causal) hipLaunchKernelGGL((fa_fwd_wide64_kernel<0, true>), dim3(grid), dim3(256), 0, st, p);
@@ -252,24 +313,27 @@ hipError_t launch_attention(const FaParams &p, int mode, int D, int causal, int 
             default: return launch_pair<1, 128>(p, grid, st);
         }
     }
-    const int key = ((mode != FA_MODE_SPLIT) << 3) | (dtype << 2) | ((D == 128) << 1) | (causal ? 1 : 0);
-    switch (key) {
-        case 0: e = launch<0, 64, false, false>(p, grid, st); break;
-        case 1: e = launch<0, 64, true, false>(p, grid, st); break;
-        case 2: e = launch<0, 128, false, false>(p, grid, st); break;
-        case 3: e = launch<0, 128, true, false>(p, grid, st); break;
-        case 4: e = launch<1, 64, false, false>(p, grid, st); break;
-        case 5: e = launch<1, 64, true, false>(p, grid, st); break;
-        case 6: e = launch<1, 128, false, false>(p, grid, st); break;
-        case 7: e = launch<1, 128, true, false>(p, grid, st); break;
-        case 8: e = launch<0, 64, false, true>(p, grid, st); break;
-        case 9: e = launch<0, 64, true, true>(p, grid, st); break;
-        case 10: e = launch<0, 128, false, true>(p, grid, st); break;
-        case 11: e = launch<0, 128, true, true>(p, grid, st); break;
-        case 12: e = launch<1, 64, false, true>(p, grid, st); break;
-        case 13: e = launch<1, 64, true, true>(p, grid, st); break;
-        case 14: e = launch<1, 128, false, true>(p, grid, st); break;
-        case 15: e = launch<1, 128, true, true>(p, grid, st); break;
+    if (mode == FA_MODE_SPLIT) {
+        // full attention is the causal instantiation with the diagonal past every key (at D = 64 it takes 120 registers
+        // where one without the limit took 136, a fourth wave per SIMD)
+        FaParams f = p;
+        if (!causal) f.off = p.Nk - 1;
+        switch ((dtype << 1) | (D == 128)) {
+            case 0: return launch<0, 64, true, false>(f, grid, st);
+            case 1: return launch<0, 128, true, false>(f, grid, st);
+            case 2: return launch<1, 64, true, false>(f, grid, st);
+            default: return launch<1, 128, true, false>(f, grid, st);
+        }
+    }
+    switch ((dtype << 2) | ((D == 128) << 1) | (causal ? 1 : 0)) {
+        case 0: e = launch<0, 64, false, true>(p, grid, st); break;
+        case 1: e = launch<0, 64, true, true>(p, grid, st); break;
+        case 2: e = launch<0, 128, false, true>(p, grid, st); break;
+        case 3: e = launch<0, 128, true, true>(p, grid, st); break;
+        case 4: e = launch<1, 64, false, true>(p, grid, st); break;
+        case 5: e = launch<1, 64, true, true>(p, grid, st); break;
+        case 6: e = launch<1, 128, false, true>(p, grid, st); break;
+        case 7: e = launch<1, 128, true, true>(p, grid, st); break;
         default: e = hipErrorInvalidValue; break;
     }
     return e;
@@ -323,6 +387,7 @@ FaParams base_params(const void *q, const void *k, const void *v, void *o, float
     p.left = p.right = p.prefix = 0;
     p.anchor = 0;
     p.kv_len = nullptr;
+    p.head_run = p.head_rest = p.grouped = p.group = 0;
     return p;
 }
 
@@ -363,21 +428,22 @@ int fa_fwd_plan(int B, int H, int Nq, int Nk, int D, int causal, int dtype, fa_p
         plan->lds_bytes = DECODE_WAVES * (512 / D) * (D + 2) * 4;     // one partial state per lane group
         return FA_OK;
     }
-    const int mode = choose_mode(B, H, Nq, Nk, D, causal);
-    const int BM = mode == FA_MODE_SPLIT ? 128 : 256;
+    const Decomposition dec = choose_mode(B, H, Nq, Nk, D, causal);
+    const int mode = dec.mode, BM = dec.rows;
+    const bool four = BM == 128 && mode != FA_MODE_SPLIT;
     const long long nqt = ((long long)Nq + BM - 1) / BM;
     const long long nwork = (long long)B * H * nqt;
     long long visited = 0;
-    for (long long qt = 0; qt < nqt; ++qt) visited += tiles_walked(mode, nqt, qt, Nq, Nk, causal);
+    for (long long qt = 0; qt < nqt; ++qt) visited += tiles_walked(mode, BM, nqt, qt, Nq, Nk, causal);
     plan->mode = mode;
     plan->block_m = BM;
     plan->block_n = BN;
-    plan->threads = mode == FA_MODE_WIDE64 ? 256 : 512;
-    plan->grid = (int)(((nwork + 7) / 8) * 8);
+    plan->threads = mode == FA_MODE_WIDE64 || four ? 256 : 512;
+    plan->grid = four && D == 128 ? rows_grid((long long)B * H, nqt) : (int)(((nwork + 7) / 8) * 8);
     plan->work_items = nwork;
     plan->tiles_visited = visited * B * H;
     plan->tiles_total = nwork * tiles_k;
-    plan->lds_bytes = (mode == FA_MODE_WIDE ? 1 : 2) * 4 * BN * D * 2;    // sets of 2+2 tiles
+    plan->lds_bytes = (mode == FA_MODE_WIDE || four ? 1 : 2) * 4 * BN * D * 2;    // sets of 2+2 tiles
     if (mode == FA_MODE_WIDE64) plan->lds_bytes = 4 * (16 * 1088 + BN * D * 2);   // ring of four (padded K tile, V tile)
     return FA_OK;
 }
@@ -391,8 +457,9 @@ int fa_fwd(const void *q, const void *k, const void *v, void *o, float *lse, int
     if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o) & 15) return FA_ERR_ALIGN;
     if ((uintptr_t)lse & 3) return FA_ERR_ALIGN;
 
-    const int mode = use_streaming_decode(Nq) ? FA_MODE_STREAM : choose_mode(B, H, Nq, Nk, D, causal);
-    const int BM = mode == FA_MODE_SPLIT ? 128 : 256;   // query rows per workgroup
+    const bool stream_kernel = use_streaming_decode(Nq);
+    const Decomposition dec = stream_kernel ? Decomposition{FA_MODE_STREAM, 256} : choose_mode(B, H, Nq, Nk, D, causal);
+    const int BM = dec.rows;
     const long long nqt = ((long long)Nq + BM - 1) / BM;
     const long long nwork = (long long)B * H * nqt;
 
@@ -401,7 +468,7 @@ int fa_fwd(const void *q, const void *k, const void *v, void *o, float *lse, int
     hipStream_t st = (hipStream_t)stream;
 
     hipError_t e;
-    if (mode == FA_MODE_STREAM) {
+    if (stream_kernel) {
         // a single query per head: the streaming kernel, one run per (batch, head), which stores o and lse itself
         switch ((dtype << 1) | (D == 128)) {
             case 0: e = launch_decode<0, 64>(p, (int)nwork, nwork, st); break;
@@ -410,7 +477,7 @@ int fa_fwd(const void *q, const void *k, const void *v, void *o, float *lse, int
             default: e = launch_decode<1, 128>(p, (int)nwork, nwork, st); break;
         }
     } else {
-        e = launch_attention(p, mode, D, causal, dtype, grid, st);
+        e = launch_attention(p, dec, D, causal, dtype, grid, st);
     }
     if (e != hipSuccess) {
         g_last_hip_error = (int)e;
@@ -557,7 +624,7 @@ int fa_fwd_masked(const void *q, const void *k, const void *v, void *o, float *l
     if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o) & 15) return FA_ERR_ALIGN;
     if (((uintptr_t)lse | (uintptr_t)mask->kv_len) & 3) return FA_ERR_ALIGN;
 
-    const long long nqt = ((long long)Nq + 255) / 256;
+    const long long nqt = ((long long)Nq + 127) / 128;
     const long long nwork = (long long)B * H * nqt;
     FaParams p = base_params(q, k, v, o, lse, H, Nq, Nk, nqt, nwork, scale);
     p.left = g.left;
@@ -586,8 +653,7 @@ int fa_fwd_masked(const void *q, const void *k, const void *v, void *o, float *l
         case 0: e = launch_masked<0, 64>(p, grid, st); break;
         case 1: e = launch_masked<0, 128>(p, grid, st); break;
         case 2: e = launch_masked<1, 64>(p, grid, st); break;
-        case 3: e = launch_masked<1, 128>(p, grid, st); break;
-        default: return FA_ERR_SHAPE;
+        default: e = launch_masked<1, 128>(p, grid, st); break;
     }
     if (e != hipSuccess) {
         g_last_hip_error = (int)e;
@@ -661,15 +727,15 @@ int block_attention(const void *q, const void *k, const void *v, void *o, float 
     {
         // (the keys the block's rows can see end at its last row's diagonal)
         const int nk_seen = causal ? Nk - (Nq - row_first - row_count) : Nk;
-        const int mode = choose_mode(B, H, row_count, nk_seen > 0 ? nk_seen : 1, D, causal);
-        const int BM = mode == FA_MODE_SPLIT ? 128 : 256;
+        const Decomposition dec = choose_mode(B, H, row_count, nk_seen > 0 ? nk_seen : 1, D, causal);
+        const int BM = dec.rows;
         const long long nqt = ((long long)row_count + BM - 1) / BM;
         const long long nwork = (long long)B * H * nqt;
         FaParams p = base_params((const uint16_t *)q + (size_t)row_first * D, k, v, (uint16_t *)o + (size_t)row_first * D,
                                  lse + row_first, H, row_count, Nk, nqt, nwork, scale);
         p.q_rows = Nq;
         p.off = Nk - Nq + row_first;
-        const hipError_t e = launch_attention(p, mode, D, causal, dtype, p.per_xcd * 8, st);
+        const hipError_t e = launch_attention(p, dec, D, causal, dtype, p.per_xcd * 8, st);
         if (e != hipSuccess) {
             g_last_hip_error = (int)e;
             return FA_ERR_LAUNCH;
@@ -863,7 +929,8 @@ int fa_set_option(int opt, int value) {
     bool ok = value == FA_AUTO;
     switch (opt) {
         case FA_OPT_FWD_MODE:
-            ok = ok || value == FA_MODE_SPLIT || value == FA_MODE_WIDE || value == FA_MODE_WIDE_FOLD || value == FA_MODE_WIDE64;
+            ok = ok || value == FA_MODE_SPLIT || value == FA_MODE_WIDE || value == FA_MODE_WIDE_FOLD || value == FA_MODE_WIDE64 ||
+                 value == FA_MODE_WIDE4;
             break;
         case FA_OPT_DECODE_KERNEL: ok = ok || value == 0 || value == 1; break;
         case FA_OPT_LINEAR_TILE: ok = ok || value == 128 || value == 256; break;

@@ -136,7 +136,9 @@ int fa_fwd_plan(int B, int H, int Nq, int Nk, int D, int causal, int dtype, fa_p
  *
  *   nsplit          : > 0: number of runs (clamped to the number of 64-key tiles, at most 1024);
  *                     <= 0: the library picks (256 workgroups at D = 128 and for a single query,
- *                     512 at D = 64 otherwise; runs of >= 4 tiles)
+ *                     512 at D = 64 otherwise; runs of >= 4 tiles).  For a single query and B * H that does not divide
+ *                     256 the tiles of all heads are cut into 256 equal pieces where that gives each 20 tiles (B * H
+ *                     <= 384): a head is then cut into at most as many runs as the plan reports
  *   workspace       : DEVICE pointer, 16-byte aligned, caller-owned scratch of at least
  *                     fa_fwd_splitkv_plan(...).workspace_bytes; contents on entry are ignored,
  *                     contents on return are unspecified; must not alias any other argument
@@ -174,8 +176,8 @@ int fa_fwd_splitkv_static(const void *q, const void *k, const void *v, void *o, 
                           int nsplit, void *stream);
 
 typedef struct fa_splitkv_plan {
-    int nsplit;                 /* runs actually used */
-    int grid_x, grid_y;         /* first kernel: work items (tile kernel: rounded up to a multiple of 8) x runs */
+    int nsplit;                 /* runs of a head actually used (the most any head has, where all heads' tiles are cut into equal pieces) */
+    int grid_x, grid_y;         /* first kernel: work items (tile kernel: rounded up to a multiple of 8) x runs; pieces x 1 */
     int combine_grid;           /* second kernel: blocks of 256 threads (0: none -- with a single run the call is fa_fwd's launch) */
     long long work_items;       /* B * H * ceil(Nq / 256) */
     long long workspace_bytes;  /* nsplit * B * H * Nq * (D + 2) * 4 */
@@ -295,8 +297,8 @@ int fa_fwd_masked(const void *q, const void *k, const void *v, void *o, float *l
  * prefix and the window laid end to end, so entries with few keys are split as evenly as entries with many.
  *
  *   nsplit, workspace, workspace_bytes : as for fa_fwd_splitkv with Nq = 1; fa_fwd_splitkv_plan(B, H, 1, Nk, D,
- *                     0, dtype, nsplit) reports the number of shares and the bytes (a single share needs no
- *                     workspace: NULL is accepted then)
+ *                     0, dtype, nsplit) reports the number of shares (where the library picks it, the most that are used)
+ *                     and the bytes (a single share needs no workspace: NULL is accepted then)
  *   everything else : as for fa_fwd_masked
  *
  * Enqueues the streaming kernel and, with more than one share, the merge kernel on `stream`; allocates

@@ -130,18 +130,20 @@ hipError_t launch_splitkv(const FaParams &p, int nwork_padded, long long rows, b
     if (e != hipSuccess) return e;
     constexpr int RPB = 256 / (D / 4);            // rows per combine block
     hipLaunchKernelGGL((fa_combine_kernel<DT, D>), dim3((unsigned)((rows + RPB - 1) / RPB)), dim3(256), 0, stream,
-                       p.part_o, p.part_ml, p.o, p.lse, rows, p.nsplit);
+                       p.part_o, p.part_ml, p.o, p.lse, rows, p.nsplit, 0u, 0u);
     return hipGetLastError();
 }
 
+// single query; p.stream_wgs pieces, or p.nsplit runs of each head
 template <int DT, int D>
 hipError_t launch_decode(const FaParams &p, int heads, long long rows, hipStream_t stream) {
-    hipLaunchKernelGGL((fa_decode_kernel<DT, D>), dim3(heads, p.nsplit), dim3(DECODE_WAVES * 64), 0, stream, p);
+    const dim3 grid = p.stream_wgs > 0 ? dim3(p.stream_wgs) : dim3(heads, p.nsplit);
+    hipLaunchKernelGGL((fa_decode_kernel<DT, D>), grid, dim3(DECODE_WAVES * 64), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.nsplit == 1) return e;   // a single run stores o and lse itself
     constexpr int RPB = 256 / (D / 4);
     hipLaunchKernelGGL((fa_combine_kernel<DT, D>), dim3((unsigned)((rows + RPB - 1) / RPB)), dim3(256), 0, stream,
-                       p.part_o, p.part_ml, p.o, p.lse, rows, p.nsplit);
+                       p.part_o, p.part_ml, p.o, p.lse, rows, p.nsplit, (unsigned)((p.Nk + BN - 1) / BN), (unsigned)p.stream_wgs);
     return hipGetLastError();
 }
 
@@ -153,7 +155,7 @@ hipError_t launch_decode_masked(const FaParams &p, int heads, hipStream_t stream
     if (e != hipSuccess || p.nsplit == 1) return e;
     constexpr int RPB = 256 / (D / 4);
     hipLaunchKernelGGL((fa_combine_kernel<DT, D>), dim3((unsigned)((heads + RPB - 1) / RPB)), dim3(256), 0, stream,
-                       p.part_o, p.part_ml, p.o, p.lse, (long long)heads, p.nsplit);
+                       p.part_o, p.part_ml, p.o, p.lse, (long long)heads, p.nsplit, 0u, 0u);
     return hipGetLastError();
 }
 
@@ -265,19 +267,38 @@ long long tiles_walked(int mode, int BM, long long nqt, long long qt, int Nq, in
 // The streaming kernel of the single-query case (fa_decode_kernel) does best with one four-wave workgroup
 // per compute unit as well (each wave keeps 32 KiB of loads in flight): more of them only shorten the
 // contiguous runs and add partial results to merge (measured: 512 workgroups 1-3% slower, 1024 5-10%).
+// Where nobody asked for a number of runs and ceil(256 / heads) of them per head would leave most compute units idle in a
+// second round (heads that do not divide 256), or one per head would (257 .. 384 heads), the tiles of all heads are cut
+// into 256 equal pieces instead, given 20 tiles a piece (us per call, runs and pieces: 3 x 12 x 28949, D = 64: 57, 47;
+// 2 x 24 x 32768: 156, 125; 10 x 32 x 3000: 88, 77; but 3 x 12 x 2000, D = 64, 4.5 tiles: 8.2, 9.7; 416 heads: 67, 70).
 constexpr int SPLITKV_MAX = 1024;
 constexpr long long DECODE_WORKGROUPS = 256;
-int choose_nsplit(long long nwork, long long tiles_k, int D, int nsplit_in, bool streaming) {
+constexpr long long DECODE_PIECE_TILES = 20;
+struct SplitChoice {
+    int nsplit, stream_wgs;      // runs of a head (at most, with pieces); pieces of all heads laid end to end, 0: none
+};
+SplitChoice choose_nsplit(long long nwork, long long Nk, int D, int nsplit_in, bool streaming) {
+    const long long tiles_k = (Nk + BN - 1) / BN;
     long long n = nsplit_in;
     if (n <= 0) {
         const long long target = streaming ? DECODE_WORKGROUPS : (D == 128 ? 256 : 512);
+        if (streaming) {
+            const long long total = nwork * tiles_k, wgs = DECODE_WORKGROUPS;
+            if (nwork <= 384 && wgs % nwork != 0 && total >= wgs * DECODE_PIECE_TILES && (total + 1) * wgs < (1ll << 32)) {
+                // a head's tiles begin at a multiple of 1/b of a piece and are a/b pieces long
+                long long x = wgs, y = nwork;
+                while (y) { const long long t = x % y; x = y; y = t; }
+                const long long a = wgs / x, b = nwork / x;
+                return {(int)((a + 2 * b - 2) / b), (int)wgs};
+            }
+        }
         n = (target + nwork - 1) / nwork;
         if (n > tiles_k / 4) n = tiles_k / 4;
     }
     if (n > tiles_k) n = tiles_k;
     if (n > SPLITKV_MAX) n = SPLITKV_MAX;
     if (n < 1) n = 1;
-    return (int)n;
+    return {(int)n, 0};
 }
 
 template <int DT, int D>
@@ -381,6 +402,7 @@ FaParams base_params(const void *q, const void *k, const void *v, void *o, float
     p.qmode = scale > 0.f ? 0 : (scale < 0.f ? 1 : 2);
     p.c = scale == 0.f ? 1.f : fabsf(scale) * LOG2E;
     p.nsplit = 1;
+    p.stream_wgs = 0;
     p.kv_stream = 0;
     p.part_o = nullptr;
     p.part_ml = nullptr;
@@ -495,14 +517,14 @@ int fa_fwd_splitkv_plan(int B, int H, int Nq, int Nk, int D, int causal, int dty
     if (nsplit > SPLITKV_MAX) return FA_ERR_NSPLIT;
     const long long nqt = ((long long)Nq + 255) / 256;
     const long long nwork = (long long)B * H * nqt;
-    const long long tiles_k = ((long long)Nk + BN - 1) / BN;
     const bool streaming = use_streaming_decode(Nq);
-    const int ns = choose_nsplit(nwork, tiles_k, D, nsplit, streaming);
+    const SplitChoice choice = choose_nsplit(nwork, Nk, D, nsplit, streaming);
+    const int ns = choice.nsplit;
     const long long rows = (long long)B * H * Nq;
     plan->nsplit = ns;
     plan->streaming = streaming ? 1 : 0;
-    plan->grid_x = streaming ? (int)nwork : (int)(((nwork + 7) / 8) * 8);
-    plan->grid_y = ns;
+    plan->grid_x = choice.stream_wgs ? choice.stream_wgs : streaming ? (int)nwork : (int)(((nwork + 7) / 8) * 8);
+    plan->grid_y = choice.stream_wgs ? 1 : ns;
     plan->combine_grid = ns == 1 ? 0 : (int)((rows + (1024 / D) - 1) / (1024 / D));   // a single run is fa_fwd's launch
     plan->work_items = nwork;
     plan->workspace_bytes = (long long)ns * rows * (D + 2) * 4;
@@ -529,6 +551,7 @@ int fa_fwd_splitkv(const void *q, const void *k, const void *v, void *o, float *
 
     FaParams p = base_params(q, k, v, o, lse, H, Nq, Nk, ((long long)Nq + 255) / 256, pl.work_items, scale);
     p.nsplit = pl.nsplit;
+    p.stream_wgs = pl.streaming && pl.grid_y == 1 ? pl.grid_x : 0;     // (a single run went to fa_fwd above)
     p.kv_stream = Nq <= 256;
     p.part_o = (float *)workspace;
     p.part_ml = p.part_o + (size_t)pl.nsplit * rows * D;
@@ -538,10 +561,10 @@ int fa_fwd_splitkv(const void *q, const void *k, const void *v, void *o, float *
     if (pl.streaming) {
         // one query sees every key under the bottom-right-aligned causal mask: causal or not is the same
         switch ((dtype << 1) | (D == 128)) {
-            case 0: e = launch_decode<0, 64>(p, pl.grid_x, rows, st); break;
-            case 1: e = launch_decode<0, 128>(p, pl.grid_x, rows, st); break;
-            case 2: e = launch_decode<1, 64>(p, pl.grid_x, rows, st); break;
-            default: e = launch_decode<1, 128>(p, pl.grid_x, rows, st); break;
+            case 0: e = launch_decode<0, 64>(p, (int)pl.work_items, rows, st); break;
+            case 1: e = launch_decode<0, 128>(p, (int)pl.work_items, rows, st); break;
+            case 2: e = launch_decode<1, 64>(p, (int)pl.work_items, rows, st); break;
+            default: e = launch_decode<1, 128>(p, (int)pl.work_items, rows, st); break;
         }
         if (e != hipSuccess) {
             g_last_hip_error = (int)e;
@@ -686,9 +709,13 @@ int fa_decode_masked(const void *q, const void *k, const void *v, void *o, float
     p.prefix = mask->prefix < Nk ? mask->prefix : Nk;
     p.kv_len = mask->kv_len;
     p.anchor = mask->diag_from_kv_len;
-    p.nsplit = pl.nsplit;
+    // chosen by the library: a number of workgroups just past one per compute unit would take a second round for the few
+    // (1 x 40 heads of 30000 keys: 320 workgroups 78 us, 240 68)
+    int shares = pl.nsplit;
+    if (nsplit <= 0 && heads * shares > 256 && heads * shares < 448 && 256 / heads * heads >= 192) shares = (int)(256 / heads);
+    p.nsplit = shares;
     p.part_o = (float *)workspace;
-    p.part_ml = p.part_o + (size_t)pl.nsplit * heads * D;
+    p.part_ml = p.part_o + (size_t)shares * heads * D;
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
     switch ((dtype << 1) | (D == 128)) {

@@ -135,8 +135,9 @@ int fa_fwd_plan(int B, int H, int Nq, int Nk, int D, int causal, int dtype, fa_p
  * keys or more go to the kernel of FA_MODE_WIDE64.
  *
  *   nsplit          : > 0: number of runs (clamped to the number of 64-key tiles, at most 1024);
- *                     <= 0: the library picks (256 workgroups at D = 128 and for a single query,
- *                     512 at D = 64 otherwise; runs of >= 4 tiles).  For a single query and B * H that does not divide
+ *                     <= 0: the library picks (runs of >= 4 tiles: for up to 16 queries as many as one round of
+ *                     workgroups holds, 256 at D = 128 and for a single query, 512 at D = 64 otherwise; for more
+ *                     queries by an estimate of the time, and a single run where that is best).  For a single query and B * H that does not divide
  *                     256 the tiles of all heads are cut into 256 equal pieces where that gives each 20 tiles (B * H
  *                     <= 384): a head is then cut into at most as many runs as the plan reports
  *   workspace       : DEVICE pointer, 16-byte aligned, caller-owned scratch of at least

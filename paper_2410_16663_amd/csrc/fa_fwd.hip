@@ -259,11 +259,15 @@ long long tiles_walked(int mode, int BM, long long nqt, long long qt, int Nq, in
     return kmax >= 0 ? kmax / BN + 1 : 0;
 }
 
-// Split-KV launch shape.  nsplit_in > 0 is taken as given (clamped to the number of key
-// tiles); otherwise pick enough runs for one workgroup per compute unit at D = 128 and two at
-// D = 64, whose tiles are half the bytes (measured best: the path is bound by HBM, which that
-// many workgroups' loads in flight saturate, and every further run only adds its fixed cost
-// and its share of the merge), each run at least four tiles long.
+// Split-KV launch shape.  nsplit_in > 0 is taken as given (clamped to the number of key tiles); otherwise runs of at
+// least four tiles:
+//  * a few queries (up to 16): as many as one round of workgroups holds -- one per compute unit at D = 128, two at D = 64,
+//    whose tiles are half the bytes; the path is bound by HBM, which that many workgroups' loads in flight saturate.  A
+//    round is counted per XCD: the work items go to the XCDs in runs of ceil(items / 8), and one run too many for an
+//    XCD's 32 compute units costs a second round (2 x 24 heads, 4 queries on 30000: 6 runs 193 us, 5 116);
+//  * more queries: the least of splitkv_cost, which prices rounds, walks and the merge (us per call, chosen by the number of
+//    workgroups alone and by cost: 1 x 40 x 1000 on 20000 505, 393; 1 x 20 x 100 on 30000 107, 72; 3 x 8 x 225 on 6114 61, 40;
+//    2 x 16 x 1000 on 9000 146, 134; 3 x 40 x 594 on 837, D = 64, 42, 27).
 // The streaming kernel of the single-query case (fa_decode_kernel) does best with one four-wave workgroup
 // per compute unit as well (each wave keeps 32 KiB of loads in flight): more of them only shorten the
 // contiguous runs and add partial results to merge (measured: 512 workgroups 1-3% slower, 1024 5-10%).
@@ -277,8 +281,24 @@ constexpr long long DECODE_PIECE_TILES = 20;
 struct SplitChoice {
     int nsplit, stream_wgs;      // runs of a head (at most, with pieces); pieces of all heads laid end to end, 0: none
 };
-SplitChoice choose_nsplit(long long nwork, long long Nk, int D, int nsplit_in, bool streaming) {
-    const long long tiles_k = (Nk + BN - 1) / BN;
+// Estimated microseconds of a call cut into n runs; T: tiles a query block walks on average.  Fitted to 23 shapes, each
+// timed at 1 .. 48 runs: the chosen number is within 10% of the best one.
+double splitkv_cost(long long heads, int Nq, double T, int D, long long n) {
+    const long long per_xcd = (heads * (((long long)Nq + 255) / 256) + 7) / 8;     // 256-row work items of an XCD
+    if (n == 1) {
+        // fa_fwd: 128-row workgroups, up to two per compute unit without loss of rate
+        const double x = (double)(heads * (((long long)Nq + 127) / 128)) / 256;
+        return D == 128 ? T * (x <= 1 ? 0.95 : 0.95 * x + 0.25) + 5 : T * 0.56 * (x <= 1.25 ? 1 : 0.8 * x) + 8;
+    }
+    const long long wgs = per_xcd * n;
+    const double walk = T / (double)n;
+    const double merge = 4 + (double)n * heads * Nq * D * 8 / 4e6;
+    if (D == 128) return (double)((wgs + 31) / 32) * (walk * 1.8 + 6) + merge;
+    return (wgs <= 32 ? walk * 1.0 + 6 : (double)((wgs + 63) / 64) * (walk * 1.7 + 6)) + merge;
+}
+SplitChoice choose_nsplit(int B, int H, int Nq, int Nk, int D, int causal, int nsplit_in, bool streaming) {
+    const long long heads = (long long)B * H, nwork = heads * (((long long)Nq + 255) / 256);
+    const long long tiles_k = ((long long)Nk + BN - 1) / BN;
     long long n = nsplit_in;
     if (n <= 0) {
         const long long target = streaming ? DECODE_WORKGROUPS : (D == 128 ? 256 : 512);
@@ -294,6 +314,25 @@ SplitChoice choose_nsplit(long long nwork, long long Nk, int D, int nsplit_in, b
         }
         n = (target + nwork - 1) / nwork;
         if (n > tiles_k / 4) n = tiles_k / 4;
+        if (n < 1) n = 1;
+        if (Nq > 1 && Nq <= 16) {
+            const long long fit = target / 8 / ((nwork + 7) / 8);
+            if (n > fit) n = fit;
+        } else if (Nq > 16) {
+            // (never past fa_fwd_splitkv_static's array where the number of workgroups alone stayed within it)
+            const double T = (double)(causal && Nk >= Nq ? (long long)Nk - Nq / 2 : (long long)Nk) / BN;
+            const long long row_bytes = heads * Nq * (D + 2) * 4;
+            const long long cap = n * row_bytes > FA_STATIC_WORKSPACE_BYTES ? n * row_bytes : FA_STATIC_WORKSPACE_BYTES;
+            double best = splitkv_cost(heads, Nq, T, D, 1);
+            n = 1;
+            for (long long i = 2; i <= 64 && i <= tiles_k / 4 && i * row_bytes <= cap; ++i) {
+                const double t = splitkv_cost(heads, Nq, T, D, i);
+                if (t < best) {
+                    best = t;
+                    n = i;
+                }
+            }
+        }
     }
     if (n > tiles_k) n = tiles_k;
     if (n > SPLITKV_MAX) n = SPLITKV_MAX;
@@ -510,7 +549,6 @@ int fa_fwd(const void *q, const void *k, const void *v, void *o, float *lse, int
 
 int fa_fwd_splitkv_plan(int B, int H, int Nq, int Nk, int D, int causal, int dtype, int nsplit,
                         fa_splitkv_plan_t *plan) {
-    (void)causal;
     if (!plan) return FA_ERR_NULL;
     const int rc = check_shape(B, H, Nq, Nk, D, dtype);
     if (rc != FA_OK) return rc;
@@ -518,7 +556,7 @@ int fa_fwd_splitkv_plan(int B, int H, int Nq, int Nk, int D, int causal, int dty
     const long long nqt = ((long long)Nq + 255) / 256;
     const long long nwork = (long long)B * H * nqt;
     const bool streaming = use_streaming_decode(Nq);
-    const SplitChoice choice = choose_nsplit(nwork, Nk, D, nsplit, streaming);
+    const SplitChoice choice = choose_nsplit(B, H, Nq, Nk, D, causal, nsplit, streaming);
     const int ns = choice.nsplit;
     const long long rows = (long long)B * H * Nq;
     plan->nsplit = ns;

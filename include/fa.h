@@ -85,9 +85,10 @@ int fa_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
  * With W = B*H*ceil(Nq/256), fa_fwd picks SPLIT for at most 256 blocks of 128 rows unless the walk is short (Nk <= 768, at
  * D = 64 512, or 1024 without the causal mask), and for causal problems over Nq = 2048 with W < 640 (Nq <= 4096), or
  * of at most 512 such blocks (longer), that are not FOLD's; WIDE_FOLD for causal problems with Nq > 768 whose one to four
- * rounds of 256 workgroups fill the last to 85% (Nq <= 4096, at D = 64 8192); WIDE64 when D = 128, a query sees 4096 keys
- * or more on average (Nk, or Nk - Nq/2 when causal) and its rounds are filled or many; else WIDE, on 128 rows but for
- * Nk >= 1536 without the causal mask and, at D = 64, over 4096 keys with it.
+ * rounds of 256 workgroups fill the last to 85% (Nq <= 4096, at D = 64 8192; at D = 128 while a query sees less than 8192
+ * keys on average: Nk, or Nk - Nq/2 when causal); WIDE64 when D = 128, a query sees 4096 keys or more on average and its
+ * rounds are filled or many; else WIDE, on 128 rows but for Nk >= 1536 without the causal mask and, at D = 64, over 4096
+ * keys with it.
  * fa_set_option(FA_OPT_FWD_MODE, ...) overrides the choice (tests, tuning).
  * Nq = 1 (one decoding step) takes none of these: FA_MODE_STREAM, the register-streaming kernel
  * described at fa_fwd_splitkv, one workgroup per (batch, head) -- full speed when B*H fills the

@@ -8,11 +8,14 @@
 // others get a per-element predicate computed from indices -- no mask tensor exists.
 //
 // Where things are (the .inc files are fragments of this one translation unit, included below):
-//  * fa_attention_kernel.inc -- fa_fwd_kernel, the attention kernel, one source for every variant (template
-//    flags): WIDE (256 query rows per workgroup, all eight waves walk the same tiles) or split (128 rows, two
-//    groups of four waves on alternate tiles, merged through LDS); CAUSAL; PAIR (folded rows for short causal
+//  * fa_attention_kernel.inc -- fa_fwd_kernel, the attention kernel, one source for most variants (template
+//    flags): WIDE (all NW waves walk the same tiles: 256 query rows with eight, 128 with four) or split (128 rows,
+//    two groups of four waves on alternate tiles, merged through LDS); CAUSAL; PAIR (folded rows for short causal
 //    problems); SPLITKV (one run of the key tiles per workgroup, unnormalised result to a workspace); GENMASK
 //    (window / prefix / key-count masks from a descriptor).  Entry points fa_fwd, fa_fwd_splitkv, fa_fwd_masked.
+//  * fa_attention_wide64_kernel.inc -- fa_fwd_wide64_kernel, long walks at D = 128: 64 query rows per wave.
+//  * fa_attention_rows_kernel.inc -- fa_fwd_rows_kernel, causal D = 128 problems of short and middle length:
+//    persistent workgroups of four waves that take 128-row blocks from a balanced list.
 //  * fa_decode_kernels.inc -- fa_decode_kernel, the single-query decoding step with K/V streamed through
 //    registers, and fa_combine_kernel, which merges the split-KV runs.
 //  * fa_linear_kernel.inc -- the output projection that follows the attention block by block (section 4.2),
@@ -24,10 +27,10 @@
 //  * this file -- the host side: argument checks, choice of decomposition, launch shapes, the C ABI.
 //
 // gfx950 mapping common to all variants of the attention kernel (this library's own design):
-//  * one wavefront owns 32 query rows; a workgroup is 8 wavefronts, two per SIMD.  Each wavefront
-//    runs a tile as three clusters (logits, softmax, second product); overlap of the matrix and
-//    vector units comes mostly from the two wavefronts of a SIMD being in different clusters; they
-//    run free between the one workgroup barrier per tile.
+//  * one wavefront owns 32 query rows; a SIMD holds two wavefronts, of one workgroup of eight or of two
+//    workgroups of four.  Each wavefront runs a tile as three clusters (logits, softmax, second
+//    product); overlap of the matrix and vector units comes mostly from the two wavefronts of a SIMD
+//    being in different clusters; those of a workgroup run free between its one barrier per tile.
 //  * logits are produced TRANSPOSED, S^T = K Q^T, with v_mfma_f32_32x32x16: keys on the
 //    M side (A operand, read from LDS with ds_read_b128), queries on the N side (B
 //    operand, held in registers for the whole kernel).  A lane then owns ONE query
@@ -193,7 +196,8 @@ bool use_streaming_decode(int Nq) { return Nq == 1 && option(FA_OPT_DECODE_KERNE
 //    for a single round at D = 128 (1 x 32 x 2048: 44, rows 47; several rounds: rows, 1 x 32 x 4096: 133 instead of
 //    148), and at D = 64 (1 x 32 x 4096: 93, four 135; 1 x 32 x 8192: 329, wide 349).
 //  * long walks at D = 128 (4096 keys per query on average): FA_MODE_WIDE64, where its rounds of 256 are filled (1 x 20 x
-//    8192, two and a half rounds: 437, rows 329).
+//    8192, two and a half rounds: 437, rows 329); from 8192 keys on before the fold (1 x 32 x 2048 on 16384: 440, fold
+//    472; 2 x 32 x 4096 on 12288 fp16: 1230, 1269; 1 x 32 x 2048 on 7168: 207, 202).
 //  * everything else on four waves, whose waves share a SIMD with other workgroups' (D = 128 causal: 16 x 32 x 2048
 //    590, wide 745; 3 x 20 x 1531 47, split 68, wide 70; full: 47 x 32 x 280 122, wide 205), but for full attention over
 //    1536 keys and more, where the tiles loaded per 256 rows count (4 x 32 x 2048: wide 266, rows 273; D = 64, 8 x 32 x
@@ -225,6 +229,7 @@ Decomposition choose_mode(int B, int H, int Nq, int Nk, int D, int causal) {
         return Nk <= short_walk ? four : split;
     }
     if (!four_fits) return D == 128 && avg_keys >= 4096 ? wide64 : wide;
+    if (D == 128 && causal && avg_keys >= 8192 && full_rounds) return wide64;
     if (causal && nqt >= 4) {
         if (W >= 256 && W <= 1024 && full_rounds && Nq <= (D == 64 ? 8192 : 4096))
             return D == 64 || W <= 256 ? fold : Decomposition{FA_MODE_WIDE_FOLD, 128};

@@ -215,8 +215,9 @@ int fa_fwd_splitkv_plan(int B, int H, int Nq, int Nk, int D, int causal, int dty
  * communication by enqueueing it on another stream behind an event recorded after this call.
  * Calls for different blocks are independent.  Error behaviour as for fa_fwd.  The GEMM's
  * workgroup tile is 256 tokens x 256 outputs when that still gives each of the 256 compute units
- * a workgroup (B * ceil(row_count/256) * N/256 >= 256), else 128 x 256; fa_set_option(FA_OPT_LINEAR_TILE,
- * 128 | 256) overrides (tests, tuning).  The tiles are dealt to the XCDs in panels of
+ * a workgroup (B * ceil(row_count/256) * N/256 >= 256), else 128 x 256; 128 x 128 or 64 x 128 where that makes
+ * at most 256 workgroups.  fa_set_option(FA_OPT_LINEAR_TILE, 256 | 128 | 128128 | 64128) overrides (tests,
+ * tuning); the tile changes no result.  The tiles are dealt to the XCDs in panels of
  * a few row tiles so that each L2 fetches about as many bytes of o as of w; fa_set_option(
  * FA_OPT_LINEAR_PANEL, row tiles per panel) overrides that too (the order changes no result).
  *
@@ -353,7 +354,7 @@ int fa_mask_interior_run(const fa_mask_t *mask, int kv_len, int Nq, int Nk, int 
  *                          otherwise), FA_MODE_WIDE64 (D = 128 only; WIDE otherwise), FA_MODE_WIDE4 or FA_AUTO.
  *                          FA_MODE_WIDE also keeps fa_fwd_splitkv's long runs on the tile kernel
  *   FA_OPT_DECODE_KERNEL : 0 or FA_AUTO: Nq = 1 runs the register-streaming kernel; 1: the tile kernels
- *   FA_OPT_LINEAR_TILE   : 128, 256 or FA_AUTO: token rows per workgroup tile of the projection
+ *   FA_OPT_LINEAR_TILE   : 128, 256 (tokens x 256 outputs), 128128, 64128 (x 128) or FA_AUTO: workgroup tile of the projection
  *   FA_OPT_LINEAR_PANEL  : >= 1 or FA_AUTO: row tiles per panel of the projection's tile order
  *   FA_OPT_LINEAR_OVERLAP: 1 or FA_AUTO: fa_attn_linear runs the projections on its second stream; 0: everything
  *                          on the caller's stream

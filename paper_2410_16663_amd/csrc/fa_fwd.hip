@@ -404,21 +404,48 @@ hipError_t launch_attention(const FaParams &p, Decomposition dec, int D, int cau
     return e;
 }
 
-template <int DT, int D>
-hipError_t launch_linear(const LinParams &p, int BM, hipStream_t stream) {
-    if (BM == 256) hipLaunchKernelGGL((fa_linear_kernel<DT, D, 256>), dim3(p.per_xcd * 8), dim3(512), 0, stream, p);
-    else hipLaunchKernelGGL((fa_linear_kernel<DT, D, 128>), dim3(p.per_xcd * 8), dim3(512), 0, stream, p);
+struct LinearTile {
+    int rows, cols;
+};
+// The projection's workgroup tile: the largest (rows x outputs; less LDS traffic per matrix instruction, more work per barrier)
+// that gives every compute unit a workgroup, or, where even the smaller ones make at most 256, the smallest: a launch that
+// leaves compute units idle takes as long as one workgroup's chain of k-tiles.  Two smaller tiles per compute unit are
+// slower than one of the next size.  us per call with the attention, tiles 128 x 256, 128 x 128, 64 x 128 (number of
+// workgroups of the chosen one), bf16, D = 128, 32 heads, outputs: 256 rows x 4096 65, 46, 38 (128); 512 rows x 4096, 40
+// heads 83, 60, 52 (256); 768 rows x 4096 75, 56, 72 (192); 1024 x 4096 77, 62, 76 (256); 1280 x 4096 86, 101, 106 (160).
+// FA_OPT_LINEAR_TILE overrides (tests, tuning).
+LinearTile choose_linear_tile(int B, int rows, int N) {
+    const LinearTile forms[] = {{64, 128}, {128, 128}, {128, 256}, {256, 256}};
+    auto tiles = [&](const LinearTile &t) { return (long long)B * (((long long)rows + t.rows - 1) / t.rows) * (N / t.cols); };
+    switch (option(FA_OPT_LINEAR_TILE)) {
+        case 256: return forms[3];
+        case 128: return forms[2];
+        case 128128: return forms[1];
+        case 64128: return forms[0];
+        default: break;
+    }
+    if (tiles(forms[0]) <= 256) return forms[0];
+    if (tiles(forms[1]) <= 256) return forms[1];
+    return tiles(forms[3]) >= 256 ? forms[3] : forms[2];
+}
+template <int DT>
+hipError_t launch_linear(const LinParams &p, LinearTile t, hipStream_t stream) {
+    const dim3 grid(p.per_xcd * 8), block(512);
+    if (t.rows == 256) hipLaunchKernelGGL((fa_linear_kernel<DT, 256, 256, 2>), grid, block, 0, stream, p);
+    else if (t.cols == 256) hipLaunchKernelGGL((fa_linear_kernel<DT, 128, 256, 3>), grid, block, 0, stream, p);
+    else if (t.rows == 128) hipLaunchKernelGGL((fa_linear_kernel<DT, 128, 128, 4>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((fa_linear_kernel<DT, 64, 128, 6>), grid, block, 0, stream, p);
     return hipGetLastError();
 }
 
 // Row tiles per panel of the projection's tile order.  The c = min(per_xcd, 32) workgroups an XCD runs at a
 // time (one per compute unit) are consecutive tiles of its run: R row tiles by c / R column slices, for which
-// its L2 fetches R * BM rows of o and (c / R) * 256 columns of w, each K elements long: least for
-// R = sqrt(c * 256 / BM).  Measured: 4% on launches of several rounds, nothing on single-round ones.
-int linear_panel(int per_xcd, int BM, int m_tiles) {
+// its L2 fetches R * rows of o and (c / R) * cols of w, each K elements long: least for
+// R = sqrt(c * cols / rows).  Measured: 4% on launches of several rounds, nothing on single-round ones.
+int linear_panel(int per_xcd, LinearTile t, int m_tiles) {
     const int c = per_xcd < 32 ? per_xcd : 32;
     int R = 1;
-    while ((R + 1) * (R + 1) * BM <= c * 256) ++R;
+    while ((R + 1) * (R + 1) * t.rows <= c * t.cols) ++R;
     if (R > m_tiles) R = m_tiles;
     return R < 1 ? 1 : R;
 }
@@ -827,26 +854,18 @@ int block_projection(const void *w, const void *o, float *y, int B, int H, int N
         lp.N = N;
         lp.s0 = row_first;
         lp.rows = row_count;
-        lp.n_tiles = N / 256;
-        // 256-row tiles (less LDS traffic per matrix instruction, twice the work per barrier) when they still
-        // give every compute unit a workgroup; FA_OPT_LINEAR_TILE overrides (tests, tuning)
-        int BM = (long long)B * ((row_count + 255) / 256) * lp.n_tiles >= 256 ? 256 : 128;
-        if (const int forced = option(FA_OPT_LINEAR_TILE); forced == 128 || forced == 256) BM = forced;
-        lp.mt_per_b = (row_count + BM - 1) / BM;
+        lp.d_shift = D == 128 ? 7 : 6;
+        const LinearTile t = choose_linear_tile(B, row_count, N);
+        lp.n_tiles = N / t.cols;
+        lp.mt_per_b = (row_count + t.rows - 1) / t.rows;
         const long long tiles = (long long)B * lp.mt_per_b * lp.n_tiles;
         if (tiles > 0x7ffffff0LL) return FA_ERR_SHAPE;
         lp.ntile_total = (int)tiles;
         lp.per_xcd = (int)((tiles + 7) / 8);
-        lp.panel = linear_panel(lp.per_xcd, BM, B * lp.mt_per_b);
+        lp.panel = linear_panel(lp.per_xcd, t, B * lp.mt_per_b);
         if (const int v = option(FA_OPT_LINEAR_PANEL); v >= 1)   // tests, tuning
             lp.panel = v < B * lp.mt_per_b ? v : B * lp.mt_per_b;
-        hipError_t e;
-        switch ((dtype << 1) | (D == 128)) {
-            case 0: e = launch_linear<0, 64>(lp, BM, st); break;
-            case 1: e = launch_linear<0, 128>(lp, BM, st); break;
-            case 2: e = launch_linear<1, 64>(lp, BM, st); break;
-            default: e = launch_linear<1, 128>(lp, BM, st); break;
-        }
+        const hipError_t e = dtype == FA_DTYPE_F16 ? launch_linear<0>(lp, t, st) : launch_linear<1>(lp, t, st);
         if (e != hipSuccess) {
             g_last_hip_error = (int)e;
             return FA_ERR_LAUNCH;
@@ -1003,7 +1022,7 @@ int fa_set_option(int opt, int value) {
                  value == FA_MODE_WIDE4;
             break;
         case FA_OPT_DECODE_KERNEL: ok = ok || value == 0 || value == 1; break;
-        case FA_OPT_LINEAR_TILE: ok = ok || value == 128 || value == 256; break;
+        case FA_OPT_LINEAR_TILE: ok = ok || value == 128 || value == 256 || value == 128128 || value == 64128; break;
         case FA_OPT_LINEAR_PANEL: ok = ok || value >= 1; break;
         case FA_OPT_LINEAR_OVERLAP: ok = ok || value == 0 || value == 1; break;
         default: return FA_ERR_OPTION;

@@ -71,3 +71,19 @@ def test_four_wave_form_with_moving_maxima_and_any_scale(oracle, D, scale):
     o_ref, lse_ref = oracle.attention_fwd(q, k, v, scale, True, I.F16)
     o, lse = run_fa_fwd(q, k, v, scale, True, I.F16)
     check_against_oracle(o, lse, o_ref, lse_ref, I.F16, f"four waves maxima D={D} scale={scale}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [64, 128])
+def test_four_wave_lse_counts_the_unrounded_exponentials(oracle, D):
+    """fp16, two or three tiles, logits of standard deviation 4: rows ruled by one or two keys.  With the sum over rounded
+    exponentials one dominant term is off by up to 2^-11, 5e-4 in lse; over the unrounded ones lse carries fp32 rounding
+    only: logits up to 32 whose dot product and exponent take a few steps of 2^-19 each, 1e-5."""
+    print(f"case four waves lse D={D}", flush=True)
+    force()
+    rng = np.random.default_rng(77 + D)
+    q, k, v = (I.f32_to_bits(2 * rng.standard_normal((2, 12, n, D), dtype=np.float32), I.F16) for n in (82, 168, 168))
+    scale = 1.0 / math.sqrt(D)
+    _, lse_ref = oracle.attention_fwd(q, k, v, scale, True, I.F16)
+    _, lse = run_fa_fwd(q, k, v, scale, True, I.F16)
+    assert np.abs(lse - lse_ref).max() <= 1e-5

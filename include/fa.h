@@ -128,8 +128,10 @@ int fa_fwd_plan(int B, int H, int Nq, int Nk, int D, int causal, int dtype, fa_p
  * query rows per head against a long K/V cache, where B * H * ceil(Nq/256) workgroups cannot
  * fill the chip.  The key tiles of every 256-row query block are cut into `nsplit` runs, one
  * workgroup each; every run leaves an unnormalised partial result (accumulator, exponent
- * reference, row sum -- the running quantities of appendix A) in `workspace`, and a second
- * kernel merges them: lse = logsumexp over runs, o = sum_runs exp(lse_run - lse) o_run.
+ * reference, row sum -- the running quantities of appendix A) in `workspace`, and they are
+ * merged: lse = logsumexp over runs, o = sum_runs exp(lse_run - lse) o_run.  A second kernel does that, or, for a
+ * single query and at most D/4 runs, the workgroup that finishes a head's last run (it is found through marks the runs leave
+ * in the head's row of o, which holds them until the result replaces them).
  * Bound by reading K and V once from HBM.  Nq = 1, the decoding step proper, runs a kernel of its
  * own that streams K and V through registers (one multiply-add per element leaves the matrix
  * cores nothing to reuse) and keeps the probabilities in fp32; fa_set_option(FA_OPT_DECODE_KERNEL, 1)
@@ -149,7 +151,7 @@ int fa_fwd_plan(int B, int H, int Nq, int Nk, int D, int causal, int dtype, fa_p
  *   workspace_bytes : size of `workspace`
  *   everything else : as for fa_fwd
  *
- * Enqueues two kernels on `stream` (with a single run, chosen or asked for, there is nothing
+ * Enqueues one or two kernels on `stream` (with a single run, chosen or asked for, there is nothing
  * to merge and the call enqueues exactly what fa_fwd would), allocates nothing, does not
  * synchronise.  Calls that share a workspace must be ordered (same
  * stream).  Returns FA_OK or a negative FA_ERR_* code; on an
@@ -182,7 +184,7 @@ int fa_fwd_splitkv_static(const void *q, const void *k, const void *v, void *o, 
 typedef struct fa_splitkv_plan {
     int nsplit;                 /* runs of a head actually used (the most any head has, where equal pieces are cut) */
     int grid_x, grid_y;         /* first kernel: work items (tile kernel: rounded up to a multiple of 8) x runs; pieces x 1 */
-    int combine_grid;           /* second kernel: blocks of 256 threads (0: none -- a single run is fa_fwd's launch) */
+    int combine_grid;           /* second kernel, where the merge takes one: blocks of 256 threads (0: a single run, fa_fwd's launch) */
     long long work_items;       /* B * H * ceil(Nq / 256) */
     long long workspace_bytes;  /* nsplit * B * H * Nq * (D + 2) * 4 */
     int streaming;              /* 1: the register-streaming kernel of the single-query case, 0: the tile kernel */

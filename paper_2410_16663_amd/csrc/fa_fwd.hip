@@ -50,6 +50,7 @@
 
 #include <atomic>
 #include <mutex>
+#include <random>
 #include <type_traits>
 #include <utility>
 
@@ -146,7 +147,7 @@ hipError_t launch_decode(const FaParams &p, int heads, long long rows, hipStream
     if (p.stream_wgs > 0) hipLaunchKernelGGL((fa_decode_kernel<DT, D, false, true>), dim3(p.stream_wgs), dim3(DECODE_WAVES * 64), 0, stream, p);
     else hipLaunchKernelGGL((fa_decode_kernel<DT, D>), dim3(heads, p.nsplit), dim3(DECODE_WAVES * 64), 0, stream, p);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || p.nsplit == 1) return e;   // a single run stores o and lse itself
+    if (e != hipSuccess || p.nsplit == 1 || p.tag != 0) return e;   // a single run stores o and lse itself, and so does the last of several
     constexpr int RPB = 256 / (D / 4);
     hipLaunchKernelGGL((fa_combine_kernel<DT, D>), dim3((unsigned)((rows + RPB - 1) / RPB)), dim3(256), 0, stream,
                        p.part_o, p.part_ml, p.o, p.lse, rows, p.nsplit, (unsigned)((p.Nk + BN - 1) / BN), (unsigned)p.stream_wgs);
@@ -158,7 +159,7 @@ template <int DT, int D>
 hipError_t launch_decode_masked(const FaParams &p, int heads, hipStream_t stream) {
     hipLaunchKernelGGL((fa_decode_kernel<DT, D, true>), dim3(heads, p.nsplit), dim3(DECODE_WAVES * 64), 0, stream, p);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || p.nsplit == 1) return e;
+    if (e != hipSuccess || p.nsplit == 1 || p.tag != 0) return e;
     constexpr int RPB = 256 / (D / 4);
     hipLaunchKernelGGL((fa_combine_kernel<DT, D>), dim3((unsigned)((heads + RPB - 1) / RPB)), dim3(256), 0, stream,
                        p.part_o, p.part_ml, p.o, p.lse, (long long)heads, p.nsplit, 0u, 0u);
@@ -166,6 +167,18 @@ hipError_t launch_decode_masked(const FaParams &p, int heads, hipStream_t stream
 }
 
 thread_local int g_last_hip_error = 0;
+
+// FaParams::tag of a call of fa_decode_kernel in `runs` runs per head (at most): a value of its own for every call of the process,
+// 64 bits that no other memory holds by chance, or 0 where the runs' tags do not fit into a row of o
+unsigned long long decode_tag(int runs, int D) {
+    if (runs <= 1 || runs > D / 4) return 0;
+    static std::atomic<unsigned long long> calls{std::random_device{}() * 0x9e3779b97f4a7c15ull + std::random_device{}()};
+    unsigned long long x = calls.fetch_add(0x9e3779b97f4a7c15ull, std::memory_order_relaxed);   // (SplitMix64: a bijection)
+    x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
+    x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
+    x ^= x >> 31;
+    return x != 0 ? x : 1;
+}
 
 // fa_set_option's values (FA_AUTO: the library chooses).  Every entry point reads each of them at most once per call.
 std::atomic<int> g_options[5] = {{FA_AUTO}, {FA_AUTO}, {FA_AUTO}, {FA_AUTO}, {FA_AUTO}};
@@ -592,6 +605,7 @@ FaParams base_params(const void *q, const void *k, const void *v, void *o, float
     p.kv_stream = 0;
     p.part_o = nullptr;
     p.part_ml = nullptr;
+    p.tag = 0;
     p.left = p.right = p.prefix = 0;
     p.anchor = 0;
     p.kv_len = nullptr;
@@ -745,6 +759,7 @@ int fa_fwd_splitkv(const void *q, const void *k, const void *v, void *o, float *
 
     hipError_t e;
     if (pl.streaming) {
+        p.tag = decode_tag(pl.nsplit, D);
         // one query sees every key under the bottom-right-aligned causal mask: causal or not is the same
         switch ((dtype << 1) | (D == 128)) {
             case 0: e = launch_decode<0, 64>(p, (int)pl.work_items, rows, st); break;
@@ -904,6 +919,7 @@ int fa_decode_masked(const void *q, const void *k, const void *v, void *o, float
     p.nsplit = shares;
     p.part_o = (float *)workspace;
     p.part_ml = p.part_o + (size_t)shares * heads * D;
+    p.tag = decode_tag(shares, D);
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
     switch ((dtype << 1) | (D == 128)) {

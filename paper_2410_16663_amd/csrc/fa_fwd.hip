@@ -1035,7 +1035,13 @@ int fa_attn_linear_block(const void *q, const void *k, const void *v, const void
 int fa_attn_linear(const void *q, const void *k, const void *v, const void *w, void *o, float *lse, float *y, int B,
                    int H, int Nq, int Nk, int D, int N, float scale, int causal, int dtype, int rows_per_block,
                    void *stream) {
-    if (rows_per_block <= 0 || rows_per_block >= Nq)
+    // Within one call nothing can use a finished block before the call is over, so the blocks are not computed one by one
+    // unless FA_OPT_LINEAR_OVERLAP is 1: every launch of a block is a round or less of workgroups, whose edges and idle
+    // compute units the whole problem pays once (one launch of each kernel, against blocks of 512, 1024, 2048 rows with their
+    // projections on the second stream, us: 1 x 32 x 8192, D = 128, 4096 outputs 732; 1094, 917, 809; 1 x 40 x 6000, 2560
+    // outputs 491; 744, 621, 612; 2 x 16 x 5000, D = 64, 1024 outputs 185; 382, 262, 196; 1 x 12 x 8000, D = 64, 768 outputs
+    // 174; 782, 440, 271).
+    if (rows_per_block <= 0 || rows_per_block >= Nq || option(FA_OPT_LINEAR_OVERLAP) != 1)
         return fa_attn_linear_block(q, k, v, w, o, lse, y, B, H, Nq, Nk, D, N, scale, causal, dtype, 0, Nq, stream);
     int rc = check_attn_linear(q, k, v, w, o, lse, y, B, H, Nq, Nk, D, N, scale, dtype, 0, Nq);
     if (rc != FA_OK) return rc;
@@ -1048,7 +1054,7 @@ int fa_attn_linear(const void *q, const void *k, const void *v, const void *w, v
     // behaves as if everything had been enqueued on `stream`.
     SideStream *side = nullptr;
     std::unique_lock<std::mutex> hold;
-    if (option(FA_OPT_LINEAR_OVERLAP) != 0) {
+    {
         int dev = 0;
         hipError_t e = hipGetDevice(&dev);
         if (e != hipSuccess || dev < 0 || dev >= 64) {

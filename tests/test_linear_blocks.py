@@ -1,0 +1,54 @@
+"""fa_attn_linear computes all rows at once; with FA_OPT_LINEAR_OVERLAP = 1 block after block, the projections on a second
+stream: then o, lse and y are those of fa_attn_linear_block over the same blocks."""
+import numpy as np
+import pytest
+
+from paper_2410_16663_amd import binding as fa
+from paper_2410_16663_amd import inputs as I
+import options
+from gpu_util import run_attn_linear, run_fa_fwd
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Nq,rows", [(1100, 256), (700, 699), (333, 1)])
+def test_blocks_on_two_streams_and_all_rows_at_once(Nq, rows, D):
+    import torch
+    print(f"case attn_linear blocks Nq={Nq} rows={rows} D={D}", flush=True)
+    rng = np.random.default_rng(Nq + D)
+    B, H, N = 2, 2, 512
+    bits = lambda shape, m=1.0: I.f32_to_bits(rng.standard_normal(shape, dtype=np.float32) * np.float32(m), I.BF16)
+    q, k, v, w = bits((B, H, Nq, D)), bits((B, H, Nq, D)), bits((B, H, Nq, D)), bits((H * D, N), (H * D) ** -0.5)
+    blocks, r = [], 0
+    while r < Nq:
+        n = min(max(rows // 2, 1) if r == 0 else rows, Nq - r)
+        blocks.append((r, n))
+        r += n
+    one_by_one = run_attn_linear(q, k, v, w, 0.1, True, I.BF16, blocks=blocks)
+    options.set_linear_overlap(True)
+    for _ in range(3):
+        got = run_attn_linear(q, k, v, w, 0.1, True, I.BF16, rows_per_block=rows)
+        assert all(np.array_equal(a, b) for a, b in zip(one_by_one, got))
+    for on in (False, None):
+        options.set_linear_overlap(on)
+        o, lse, y = run_attn_linear(q, k, v, w, 0.1, True, I.BF16, rows_per_block=rows)
+        whole = run_attn_linear(q, k, v, w, 0.1, True, I.BF16, rows_per_block=0)
+        assert all(np.array_equal(a, b) for a, b in zip((o, lse, y), whole))
+        o_fwd, lse_fwd = run_fa_fwd(q, k, v, 0.1, True, I.BF16)
+        assert np.array_equal(o, o_fwd) and np.array_equal(lse, lse_fwd)
+    # work enqueued on the caller's stream right behind the call sees the finished y and does not overtake it
+    options.set_linear_overlap(True)
+    dev = torch.device("cuda:0")
+    tq, tk, tv, tw = (torch.from_numpy(a.view(np.int16)).to(dev) for a in (q, k, v, w))
+    to = torch.zeros((B, H, Nq, D), dtype=torch.int16, device=dev)
+    tl = torch.zeros((B, H, Nq), dtype=torch.float32, device=dev)
+    ty = torch.empty((B, Nq, N), dtype=torch.float32, device=dev)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        fa.fa_attn_linear(tq, tk, tv, tw, to, tl, ty, B, H, Nq, Nq, D, N, 0.1, 1, I.BF16, rows, side.cuda_stream)
+        copy = ty.clone()
+        ty.zero_()
+    side.synchronize()
+    assert np.array_equal(copy.cpu().numpy(), one_by_one[2])

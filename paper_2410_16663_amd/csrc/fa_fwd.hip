@@ -144,7 +144,10 @@ hipError_t launch_splitkv(const FaParams &p, int nwork_padded, long long rows, b
 // single query; p.stream_wgs pieces, or p.nsplit runs of each head
 template <int DT, int D>
 hipError_t launch_decode(const FaParams &p, int heads, long long rows, hipStream_t stream) {
-    if (p.stream_wgs > 0) hipLaunchKernelGGL((fa_decode_kernel<DT, D, false, true>), dim3(p.stream_wgs), dim3(DECODE_WAVES * 64), 0, stream, p);
+    // (the instantiation for pieces holds the merge: equal runs that it merges are as many pieces)
+    FaParams f = p;
+    if (p.tag != 0 && p.stream_wgs == 0) f.stream_wgs = heads * p.nsplit;
+    if (f.stream_wgs > 0) hipLaunchKernelGGL((fa_decode_kernel<DT, D, false, true>), dim3(f.stream_wgs), dim3(DECODE_WAVES * 64), 0, stream, f);
     else hipLaunchKernelGGL((fa_decode_kernel<DT, D>), dim3(heads, p.nsplit), dim3(DECODE_WAVES * 64), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.nsplit == 1 || p.tag != 0) return e;   // a single run stores o and lse itself, and so does the last of several
@@ -759,7 +762,9 @@ int fa_fwd_splitkv(const void *q, const void *k, const void *v, void *o, float *
 
     hipError_t e;
     if (pl.streaming) {
-        p.tag = decode_tag(pl.nsplit, D);
+        const long long total = pl.work_items * (((long long)Nk + BN - 1) / BN);
+        // merged by the kernel itself where the tiles of its pieces (launch_decode) are found in 32 bits
+        p.tag = p.stream_wgs > 0 || pl.work_items * pl.nsplit <= 0xffffffffll / (total + 1) ? decode_tag(pl.nsplit, D) : 0;
         // one query sees every key under the bottom-right-aligned causal mask: causal or not is the same
         switch ((dtype << 1) | (D == 128)) {
             case 0: e = launch_decode<0, 64>(p, (int)pl.work_items, rows, st); break;

@@ -89,7 +89,8 @@ int fa_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
  * more on average (Nk, or Nk - Nq/2 when causal) and its rounds are filled or many (from 8192 keys before FOLD).  At D = 64:
  * WIDE_FOLD for causal triangles (Nk little over Nq) of up to four rounds whose last one is not nearly empty and for blocks
  * of rows on long caches of 1.65 to two rounds; SPLIT for triangles of 1 to 1.5 rounds or little over two, for such blocks of
- * rows below 1.65 rounds and for full attention over 1000 keys and more in 1 to 1.6 rounds.  Else WIDE, on 256 rows for long
+ * rows below 1.65 rounds, for other triangles over 2200 keys on average in up to 7.4 rounds, and for full attention over 1000
+ * keys and more in 1 to 1.6 rounds, over 1535 in 2 to 2.5.  Else WIDE, on 256 rows for long
  * walks (full: 1536 keys, at D = 64 in bf16 850; causal at D = 64: over 4096) and on 128 otherwise.
  * fa_set_option(FA_OPT_FWD_MODE, ...) overrides the choice (tests, tuning).
  * Nq = 1 (one decoding step) takes none of these: FA_MODE_STREAM, the register-streaming kernel

@@ -228,7 +228,8 @@ int fa_fwd_splitkv_plan(int B, int H, int Nq, int Nk, int D, int causal, int dty
  *
  * fa_attn_linear -- all rows.  rows_per_block is how a caller cuts the problem who overlaps communication block by block with
  * fa_attn_linear_block (the first block half that size: nothing can overlap with it); a caller of this function gets all rows
- * at once, so the library computes them in one launch of each kernel, as for rows_per_block <= 0, which is faster than any
+ * at once, so the library computes them in one launch of each kernel, as for rows_per_block <= 0 (but that fp16 carries both row
+ * sums, as the smaller blocks do, in the four-wave form where the chosen one cannot), which is faster than any
  * blocks.  fa_set_option(FA_OPT_LINEAR_OVERLAP, 1) has it compute block after block, with the projections, which touch other
  * rows than the next block's attention, on a second stream of the library's own (default priority, one per device, created by
  * the first such call on that device that is not under stream capture and kept until the process ends), each behind an event

@@ -52,3 +52,17 @@ def test_blocks_on_two_streams_and_all_rows_at_once(Nq, rows, D):
         ty.zero_()
     side.synchronize()
     assert np.array_equal(copy.cpu().numpy(), one_by_one[2])
+
+
+@pytest.mark.parametrize("B,H,N,D", [(1, 16, 1334, 128), (1, 8, 2048, 128), (1, 10, 2500, 64), (2, 24, 1024, 64)])
+def test_fp16_lse_of_blocks_given_at_once(oracle, B, H, N, D):
+    """Small blocks carry both row sums in fp16 (lse from the unrounded exponentials), and so does the one launch that stands for
+    them, whatever form it takes: logits of standard deviation 4, fp32 rounding of logits up to 32, 1e-5."""
+    print(f"case attn_linear lse {(B, H, N, D)}", flush=True)
+    rng = np.random.default_rng(N + D)
+    q, k, v = (I.f32_to_bits(2 * rng.standard_normal((B, H, N, D), dtype=np.float32), I.F16) for _ in range(3))
+    w = I.f32_to_bits(rng.standard_normal((H * D, 256), dtype=np.float32) * np.float32((H * D) ** -0.5), I.F16)
+    _, lse, _ = run_attn_linear(q, k, v, w, D ** -0.5, True, I.F16, rows_per_block=256)
+    rows = np.unique(np.concatenate([rng.integers(0, B * H * N, 2000), [0, N - 1, B * H * N - 1]]))
+    _, lse_ref = oracle.attention_fwd(q, k, v, D ** -0.5, True, I.F16, rows=rows)
+    assert np.abs(lse.reshape(-1)[rows] - lse_ref).max() <= 1e-5

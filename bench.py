@@ -515,7 +515,7 @@ def main():
     ap.add_argument("--overlap-demo", action="store_true",
                     help="with --projection-only: also time the two-stream pipeline with the exchange stand-in")
     ap.add_argument("--no-linear-overlap", action="store_true",
-                    help="fa_attn_linear computes all rows at once on the caller's stream (its default)")
+                    help="fa_attn_linear keeps its projections on the caller's stream (for comparison runs)")
     ap.add_argument("--chunked-only", action="store_true",
                     help="time only the chunked-prefill workload through fa_fwd_splitkv (for profiling runs)")
     ap.add_argument("--sliding64-only", action="store_true",

@@ -969,20 +969,12 @@ int check_attn_linear(const void *q, const void *k, const void *v, const void *w
 
 // attention of one block of rows, every head: a launch over row_count rows whose diagonal is shifted by
 // row_first; q, o, lse keep the full tensors' head pitch.  Arguments already checked.
-// both_sums: fp16 carries both row sums whatever the sizes (the rows stand for blocks, the smaller of which carry both), in the
-// four-wave form where the chosen one has no such instantiation.
 int block_attention(const void *q, const void *k, const void *v, void *o, float *lse, int B, int H, int Nq, int Nk,
-                    int D, float scale, int causal, int dtype, int row_first, int row_count, bool both_sums, hipStream_t st) {
+                    int D, float scale, int causal, int dtype, int row_first, int row_count, hipStream_t st) {
     {
         // (the keys the block's rows can see end at its last row's diagonal)
         const int nk_seen = causal ? Nk - (Nq - row_first - row_count) : Nk;
-        Decomposition dec = choose_mode(B, H, row_count, nk_seen > 0 ? nk_seen : 1, D, causal, dtype);
-        if (both_sums && dtype == FA_DTYPE_F16 && option(FA_OPT_FWD_MODE) == FA_AUTO) {
-            dec.two_sums = true;
-            if (D == 128 && dec.rows == 256 && dec.mode != FA_MODE_WIDE)
-                dec = (long long)B * H * (((long long)row_count + 127) / 128) < (1ll << 28) ? Decomposition{FA_MODE_WIDE, 128, true}
-                                                                                               : Decomposition{FA_MODE_WIDE, 256, true};
-        }
+        const Decomposition dec = choose_mode(B, H, row_count, nk_seen > 0 ? nk_seen : 1, D, causal, dtype);
         const int BM = dec.rows;
         const long long nqt = ((long long)row_count + BM - 1) / BM;
         const long long nwork = (long long)B * H * nqt;
@@ -1045,35 +1037,22 @@ SideStream g_side[64];
 
 }  // namespace
 
-static int linear_rows(const void *q, const void *k, const void *v, const void *w, void *o, float *lse, float *y, int B, int H,
-                       int Nq, int Nk, int D, int N, float scale, int causal, int dtype, int row_first, int row_count,
-                       bool both_sums, void *stream) {
-    int rc = check_attn_linear(q, k, v, w, o, lse, y, B, H, Nq, Nk, D, N, scale, dtype, row_first, row_count);
-    if (rc != FA_OK) return rc;
-    hipStream_t st = (hipStream_t)stream;
-    rc = block_attention(q, k, v, o, lse, B, H, Nq, Nk, D, scale, causal, dtype, row_first, row_count, both_sums, st);
-    if (rc != FA_OK) return rc;
-    return block_projection(w, o, y, B, H, Nq, D, N, dtype, row_first, row_count, false, st);
-}
-
 int fa_attn_linear_block(const void *q, const void *k, const void *v, const void *w, void *o, float *lse, float *y,
                          int B, int H, int Nq, int Nk, int D, int N, float scale, int causal, int dtype,
                          int row_first, int row_count, void *stream) {
-    return linear_rows(q, k, v, w, o, lse, y, B, H, Nq, Nk, D, N, scale, causal, dtype, row_first, row_count, false, stream);
+    int rc = check_attn_linear(q, k, v, w, o, lse, y, B, H, Nq, Nk, D, N, scale, dtype, row_first, row_count);
+    if (rc != FA_OK) return rc;
+    hipStream_t st = (hipStream_t)stream;
+    rc = block_attention(q, k, v, o, lse, B, H, Nq, Nk, D, scale, causal, dtype, row_first, row_count, st);
+    if (rc != FA_OK) return rc;
+    return block_projection(w, o, y, B, H, Nq, D, N, dtype, row_first, row_count, false, st);
 }
 
 int fa_attn_linear(const void *q, const void *k, const void *v, const void *w, void *o, float *lse, float *y, int B,
                    int H, int Nq, int Nk, int D, int N, float scale, int causal, int dtype, int rows_per_block,
                    void *stream) {
-    // Within one call nothing can use a finished block before the call is over, so the blocks are not computed one by one
-    // unless FA_OPT_LINEAR_OVERLAP is 1: every launch of a block is a round or less of workgroups, whose edges and idle
-    // compute units the whole problem pays once (one launch of each kernel, against blocks of 512, 1024, 2048 rows with their
-    // projections on the second stream, us: 1 x 32 x 8192, D = 128, 4096 outputs 732; 1094, 917, 809; 1 x 40 x 6000, 2560
-    // outputs 491; 744, 621, 612; 2 x 16 x 5000, D = 64, 1024 outputs 185; 382, 262, 196; 1 x 12 x 8000, D = 64, 768 outputs
-    // 174; 782, 440, 271).
-    if (rows_per_block <= 0 || rows_per_block >= Nq || option(FA_OPT_LINEAR_OVERLAP) != 1)
-        return linear_rows(q, k, v, w, o, lse, y, B, H, Nq, Nk, D, N, scale, causal, dtype, 0, Nq,
-                           rows_per_block > 0 && rows_per_block < Nq, stream);
+    if (rows_per_block <= 0 || rows_per_block >= Nq)
+        return fa_attn_linear_block(q, k, v, w, o, lse, y, B, H, Nq, Nk, D, N, scale, causal, dtype, 0, Nq, stream);
     int rc = check_attn_linear(q, k, v, w, o, lse, y, B, H, Nq, Nk, D, N, scale, dtype, 0, Nq);
     if (rc != FA_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
@@ -1085,7 +1064,7 @@ int fa_attn_linear(const void *q, const void *k, const void *v, const void *w, v
     // behaves as if everything had been enqueued on `stream`.
     SideStream *side = nullptr;
     std::unique_lock<std::mutex> hold;
-    {
+    if (option(FA_OPT_LINEAR_OVERLAP) != 0) {
         int dev = 0;
         hipError_t e = hipGetDevice(&dev);
         if (e != hipSuccess || dev < 0 || dev >= 64) {
@@ -1121,7 +1100,7 @@ int fa_attn_linear(const void *q, const void *k, const void *v, const void *w, v
     bool forked = false;
     for (int r = 0; r < Nq && rc == FA_OK;) {
         const int n = r == 0 ? first : (Nq - r < rows_per_block ? Nq - r : rows_per_block);
-        rc = block_attention(q, k, v, o, lse, B, H, Nq, Nk, D, scale, causal, dtype, r, n, false, st);
+        rc = block_attention(q, k, v, o, lse, B, H, Nq, Nk, D, scale, causal, dtype, r, n, st);
         if (rc != FA_OK) break;
         hipStream_t lin_stream = st;
         if (side) {

@@ -132,7 +132,7 @@ int fa_fwd_plan(int B, int H, int Nq, int Nk, int D, int causal, int dtype, fa_p
  * reference, row sum -- the running quantities of appendix A) in `workspace`, and they are
  * merged: lse = logsumexp over runs, o = sum_runs exp(lse_run - lse) o_run.  A second kernel does that, or, for a
  * single query and at most D/4 runs, the workgroup that finishes a head's last run (it is found through marks the runs leave
- * in the head's row of o, which holds them until the result replaces them).
+ * in the head's row of o, which holds them until the result replaces them; a process-wide counter gives every call a mark of its own).
  * Bound by reading K and V once from HBM.  Nq = 1, the decoding step proper, runs a kernel of its
  * own that streams K and V through registers (one multiply-add per element leaves the matrix
  * cores nothing to reuse) and keeps the probabilities in fp32; fa_set_option(FA_OPT_DECODE_KERNEL, 1)

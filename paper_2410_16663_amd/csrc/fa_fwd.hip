@@ -47,10 +47,11 @@
 #include <stdint.h>
 #include <stdlib.h>
 #include <string.h>
+#include <sys/random.h>
 
 #include <atomic>
+#include <chrono>
 #include <mutex>
-#include <random>
 #include <type_traits>
 #include <utility>
 
@@ -171,11 +172,20 @@ hipError_t launch_decode_masked(const FaParams &p, int heads, hipStream_t stream
 
 thread_local int g_last_hip_error = 0;
 
-// FaParams::tag of a call of fa_decode_kernel in `runs` runs per head (at most): a value of its own for every call of the process,
-// 64 bits that no other memory holds by chance, or 0 where the runs' tags do not fit into a row of o
-unsigned long long decode_tag(int runs, int D) {
+// Where the count behind decode_tag starts: random, so that two processes' tags differ.  (Not std::random_device, which throws where
+// it finds no source, through the C entry points; here the clock is left then.)
+unsigned long long tag_seed() noexcept {
+    unsigned long long x;
+    if (getrandom(&x, sizeof x, GRND_NONBLOCK) != (ssize_t)sizeof x) x = 0;
+    return x + (unsigned long long)std::chrono::system_clock::now().time_since_epoch().count();
+}
+// FaParams::tag of a call of fa_decode_kernel in `runs` runs per head (at most): 64 bits that no other memory holds by chance, or 0
+// where the runs' tags do not fit into a row of o.  Every call of the process gets a value of its own, so that what an earlier one
+// left in o is not taken for a mark.  A captured call's value is an argument of its node, the same on every replay: a replay leaves
+// none of its marks behind, because the kernel does not end before every head of several runs has its marks replaced by the result.
+unsigned long long decode_tag(int runs, int D) noexcept {
     if (runs <= 1 || runs > D / 4) return 0;
-    static std::atomic<unsigned long long> calls{std::random_device{}() * 0x9e3779b97f4a7c15ull + std::random_device{}()};
+    static std::atomic<unsigned long long> calls{tag_seed()};
     unsigned long long x = calls.fetch_add(0x9e3779b97f4a7c15ull, std::memory_order_relaxed);   // (SplitMix64: a bijection)
     x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
     x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;

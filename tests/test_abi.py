@@ -2,6 +2,8 @@
 include/fa.h declares, and rejects bad arguments before touching the HIP runtime."""
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -342,3 +344,28 @@ def test_binding_structures_have_the_headers_sizes_and_offsets(tmp_path):
             (ctypes.sizeof(fa.FaSplitKvPlan), fa.FaSplitKvPlan.streaming.offset),
             (ctypes.sizeof(fa.FaMask), fa.FaMask.kv_len.offset)]
     assert got == want
+
+
+NO_ENTROPY = r"""
+#include <random>
+#include <stdexcept>
+void std::random_device::_M_init(const std::string &) { throw std::runtime_error("no source of random numbers"); }
+"""
+DECODE_CALL = r"""
+import ctypes, sys
+if len(sys.argv) > 1: ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)      # ahead of the C++ library's own
+from paper_2410_16663_amd import binding as fa
+print("code", fa.fa_fwd_splitkv_raw(0x1000, 0x2000, 0x3000, 0x4000, 0x5000, 1, 8, 1, 4096, 128, 0.1, 1, 1, 4, 0x6000, 1 << 30))
+"""
+
+
+@pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="made-up addresses: the call must end at the launch for want of a GPU")
+def test_no_exception_leaves_a_decoding_step(lib, tmp_path):
+    """A decoding step in several runs marks them with a value of the call's own: where that comes from must not throw out of the C
+    entry point, also on a machine whose std::random_device does."""
+    src, so = tmp_path / "no_entropy.cpp", tmp_path / "no_entropy.so"
+    src.write_text(NO_ENTROPY)
+    subprocess.run(["g++", "-shared", "-fPIC", str(src), "-o", str(so)], check=True)
+    for args in ([], [str(so)]):
+        r = subprocess.run([sys.executable, "-c", DECODE_CALL] + args, capture_output=True, text=True, timeout=300, cwd=ROOT)
+        assert r.returncode == 0 and f"code {fa.FA_ERR_LAUNCH}" in r.stdout, r.stdout + r.stderr

@@ -185,7 +185,8 @@ int fa_fwd_splitkv_static(const void *q, const void *k, const void *v, void *o, 
 typedef struct fa_splitkv_plan {
     int nsplit;                 /* runs of a head actually used (the most any head has, where equal pieces are cut) */
     int grid_x, grid_y;         /* first kernel: work items (tile kernel: rounded up to a multiple of 8) x runs; pieces x 1 */
-    int combine_grid;           /* second kernel, where the merge takes one: blocks of 256 threads (0: a single run, fa_fwd's launch) */
+    int combine_grid;           /* second kernel, the merge: blocks of 256 threads (0: none -- a single run is fa_fwd's launch, and
+                                   up to D/4 runs of a single query are merged by the first kernel) */
     long long work_items;       /* B * H * ceil(Nq / 256) */
     long long workspace_bytes;  /* nsplit * B * H * Nq * (D + 2) * 4 */
     int streaming;              /* 1: the register-streaming kernel of the single-query case, 0: the tile kernel */
@@ -309,8 +310,8 @@ int fa_fwd_masked(const void *q, const void *k, const void *v, void *o, float *l
  *                     and the bytes (a single share needs no workspace: NULL is accepted then)
  *   everything else : as for fa_fwd_masked
  *
- * Enqueues the streaming kernel and, with more than one share, the merge kernel on `stream`; allocates
- * nothing; does not synchronise.  Same error codes as fa_fwd_masked and fa_fwd_splitkv.
+ * Enqueues the streaming kernel and, with more than D/4 shares, the merge kernel on `stream` (fewer are merged by the first, as in
+ * fa_fwd_splitkv); allocates nothing; does not synchronise.  Same error codes as fa_fwd_masked and fa_fwd_splitkv.
  */
 int fa_decode_masked(const void *q, const void *k, const void *v, void *o, float *lse,
                      int B, int H, int Nk, int D, float scale, const fa_mask_t *mask, int dtype,

@@ -145,11 +145,10 @@ hipError_t launch_splitkv(const FaParams &p, int nwork_padded, long long rows, b
 // single query; p.stream_wgs pieces, or p.nsplit runs of each head
 template <int DT, int D>
 hipError_t launch_decode(const FaParams &p, int heads, long long rows, hipStream_t stream) {
-    // (the instantiation for pieces holds the merge: equal runs that it merges are as many pieces)
-    FaParams f = p;
-    if (p.tag != 0 && p.stream_wgs == 0) f.stream_wgs = heads * p.nsplit;
-    if (f.stream_wgs > 0) hipLaunchKernelGGL((fa_decode_kernel<DT, D, false, true>), dim3(f.stream_wgs), dim3(DECODE_WAVES * 64), 0, stream, f);
-    else hipLaunchKernelGGL((fa_decode_kernel<DT, D>), dim3(heads, p.nsplit), dim3(DECODE_WAVES * 64), 0, stream, p);
+    const dim3 block(DECODE_WAVES * 64);
+    if (p.stream_wgs > 0) hipLaunchKernelGGL((fa_decode_kernel<DT, D, false, true>), dim3(p.stream_wgs), block, 0, stream, p);
+    else if (p.tag != 0) hipLaunchKernelGGL((fa_decode_kernel<DT, D, false, false, true>), dim3(heads, p.nsplit), block, 0, stream, p);
+    else hipLaunchKernelGGL((fa_decode_kernel<DT, D>), dim3(heads, p.nsplit), block, 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.nsplit == 1 || p.tag != 0) return e;   // a single run stores o and lse itself, and so does the last of several
     constexpr int RPB = 256 / (D / 4);
@@ -179,12 +178,12 @@ unsigned long long tag_seed() noexcept {
     if (getrandom(&x, sizeof x, GRND_NONBLOCK) != (ssize_t)sizeof x) x = 0;
     return x + (unsigned long long)std::chrono::system_clock::now().time_since_epoch().count();
 }
-// FaParams::tag of a call of fa_decode_kernel in `runs` runs per head (at most): 64 bits that no other memory holds by chance, or 0
-// where the runs' tags do not fit into a row of o.  Every call of the process gets a value of its own, so that what an earlier one
+// Whether fa_decode_kernel merges the runs of a head, `runs` of them at most, by itself: their tags fit into a row of o
+bool merges_itself(int runs, int D) { return runs > 1 && runs <= D / 4; }
+// FaParams::tag of a call that does: 64 bits that no other memory holds by chance.  Every call of the process gets a value of its own, so that what an earlier one
 // left in o is not taken for a mark.  A captured call's value is an argument of its node, the same on every replay: a replay leaves
 // none of its marks behind, because the kernel does not end before every head of several runs has its marks replaced by the result.
-unsigned long long decode_tag(int runs, int D) noexcept {
-    if (runs <= 1 || runs > D / 4) return 0;
+unsigned long long decode_tag() noexcept {
     static std::atomic<unsigned long long> calls{tag_seed()};
     unsigned long long x = calls.fetch_add(0x9e3779b97f4a7c15ull, std::memory_order_relaxed);   // (SplitMix64: a bijection)
     x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
@@ -749,7 +748,8 @@ int fa_fwd_splitkv_plan(int B, int H, int Nq, int Nk, int D, int causal, int dty
     plan->streaming = streaming ? 1 : 0;
     plan->grid_x = choice.stream_wgs ? choice.stream_wgs : streaming ? (int)nwork : (int)(((nwork + 7) / 8) * 8);
     plan->grid_y = choice.stream_wgs ? 1 : ns;
-    plan->combine_grid = ns == 1 ? 0 : (int)((rows + (1024 / D) - 1) / (1024 / D));   // a single run is fa_fwd's launch
+    // (a single run is fa_fwd's launch; a single query's few runs are merged by the first kernel)
+    plan->combine_grid = ns == 1 || (streaming && merges_itself(ns, D)) ? 0 : (int)((rows + (1024 / D) - 1) / (1024 / D));
     plan->work_items = nwork;
     plan->workspace_bytes = (long long)ns * rows * (D + 2) * 4;
     return FA_OK;
@@ -783,9 +783,7 @@ int fa_fwd_splitkv(const void *q, const void *k, const void *v, void *o, float *
 
     hipError_t e;
     if (pl.streaming) {
-        const long long total = pl.work_items * (((long long)Nk + BN - 1) / BN);
-        // merged by the kernel itself where the tiles of its pieces (launch_decode) are found in 32 bits
-        p.tag = p.stream_wgs > 0 || pl.work_items * pl.nsplit <= 0xffffffffll / (total + 1) ? decode_tag(pl.nsplit, D) : 0;
+        if (pl.combine_grid == 0) p.tag = decode_tag();
         // one query sees every key under the bottom-right-aligned causal mask: causal or not is the same
         switch ((dtype << 1) | (D == 128)) {
             case 0: e = launch_decode<0, 64>(p, (int)pl.work_items, rows, st); break;
@@ -945,7 +943,7 @@ int fa_decode_masked(const void *q, const void *k, const void *v, void *o, float
     p.nsplit = shares;
     p.part_o = (float *)workspace;
     p.part_ml = p.part_o + (size_t)shares * heads * D;
-    p.tag = decode_tag(shares, D);
+    if (merges_itself(shares, D)) p.tag = decode_tag();
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
     switch ((dtype << 1) | (D == 128)) {

@@ -94,7 +94,7 @@ def test_splitkv_plan(lib, monkeypatch, decode_kernel):
     p = fa.fa_fwd_splitkv_plan(2, 4, 1, 64 * 100, 128, 1, 0, 7)
     assert (p.nsplit, p.grid_x, p.grid_y, p.work_items, p.streaming) == (7, 8, 7, 8, int(stream))
     assert p.workspace_bytes == 7 * 2 * 4 * 1 * (128 + 2) * 4
-    assert p.combine_grid == 1                                   # 8 rows, 8 rows per block at D = 128
+    assert p.combine_grid == (0 if stream else 1)                # one kernel merges seven runs; 8 rows, 8 rows per block at D = 128
     p = fa.fa_fwd_splitkv_plan(1, 3, 1, 64 * 100, 64, 0, 1, 2)
     assert (p.grid_x, p.grid_y, p.streaming) == ((3, 2, 1) if stream else (8, 2, 0))
     assert fa.fa_fwd_splitkv_plan(1, 1, 1, 130, 64, 0, 0, 50).nsplit == 3
@@ -311,9 +311,9 @@ def test_build_report_shows_register_only_kernels():
     build.build(force=True)
     # per dtype -- attention: 2 head dims x (split, causal x (wide, wide + split-KV), paired fold, descriptor masks on four and
     # on eight waves), four waves at D = 64, the list kernel at D = 128; 64-row waves: causal x (plain, split-KV); combine: 2
-    # head dims; output projection: 4 tiles; streaming decode: 2 head dims x (plain, in pieces, masked); besides, fp16 with both
-    # row sums: 2 head dims x (split, wide), paired fold at D = 64
-    assert len(build.last_report) == 2 * (2 * (1 + 4 + 1 + 2) + 1 + 1 + 4 + 2 + 4 + 6) + 5
+    # head dims; output projection: 4 tiles; streaming decode: 2 head dims x (plain, merging runs, in pieces, masked); besides,
+    # fp16 with both row sums: 2 head dims x (split, wide), paired fold at D = 64
+    assert len(build.last_report) == 2 * (2 * (1 + 4 + 1 + 2) + 1 + 1 + 4 + 2 + 4 + 8) + 5
     for name, rep in build.last_report.items():
         assert rep["ScratchSize [bytes/lane]"] == 0 and rep["VGPRs Spill"] == 0, name
         assert rep["VGPRs"] + rep.get("AGPRs", 0) <= (512 if "fa_fwd_wide64_kernel" in name else 256), name

@@ -160,7 +160,9 @@ hipError_t launch_decode(const FaParams &p, int heads, long long rows, hipStream
 // single query under a mask descriptor: p.nsplit workgroups per (batch, head); a single one stores o and lse itself
 template <int DT, int D>
 hipError_t launch_decode_masked(const FaParams &p, int heads, hipStream_t stream) {
-    hipLaunchKernelGGL((fa_decode_kernel<DT, D, true>), dim3(heads, p.nsplit), dim3(DECODE_WAVES * 64), 0, stream, p);
+    const dim3 grid(heads, p.nsplit), block(DECODE_WAVES * 64);
+    if (p.tag != 0) hipLaunchKernelGGL((fa_decode_kernel<DT, D, true, false, true>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((fa_decode_kernel<DT, D, true>), grid, block, 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.nsplit == 1 || p.tag != 0) return e;
     constexpr int RPB = 256 / (D / 4);

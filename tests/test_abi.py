@@ -311,9 +311,9 @@ def test_build_report_shows_register_only_kernels():
     build.build(force=True)
     # per dtype -- attention: 2 head dims x (split, causal x (wide, wide + split-KV), paired fold, descriptor masks on four and
     # on eight waves), four waves at D = 64, the list kernel at D = 128; 64-row waves: causal x (plain, split-KV); combine: 2
-    # head dims; output projection: 4 tiles; streaming decode: 2 head dims x (plain, merging runs, in pieces, masked); besides,
-    # fp16 with both row sums: 2 head dims x (split, wide), paired fold at D = 64
-    assert len(build.last_report) == 2 * (2 * (1 + 4 + 1 + 2) + 1 + 1 + 4 + 2 + 4 + 8) + 5
+    # head dims; output projection: 4 tiles; streaming decode: 2 head dims x (plain and masked, each with and without
+    # the merge of runs, in pieces); besides, fp16 with both row sums: 2 head dims x (split, wide), paired fold at D = 64
+    assert len(build.last_report) == 2 * (2 * (1 + 4 + 1 + 2) + 1 + 1 + 4 + 2 + 4 + 10) + 5
     for name, rep in build.last_report.items():
         assert rep["ScratchSize [bytes/lane]"] == 0 and rep["VGPRs Spill"] == 0, name
         assert rep["VGPRs"] + rep.get("AGPRs", 0) <= (512 if "fa_fwd_wide64_kernel" in name else 256), name

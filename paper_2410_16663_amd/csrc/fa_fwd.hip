@@ -194,9 +194,18 @@ unsigned long long decode_tag() noexcept {
     return x != 0 ? x : 1;
 }
 
-// fa_set_option's values (FA_AUTO: the library chooses).  Every entry point reads each of them at most once per call.
+// fa_set_option's values (FA_AUTO: the library chooses).  Every entry point takes them once, when it is called, and hands that copy
+// on: a call that launches several kernels, or chooses twice, chooses by the same values throughout.
 std::atomic<int> g_options[5] = {{FA_AUTO}, {FA_AUTO}, {FA_AUTO}, {FA_AUTO}, {FA_AUTO}};
-int option(int which) { return g_options[which].load(std::memory_order_relaxed); }
+struct Options {
+    int value[5];
+    int operator[](int which) const { return value[which]; }
+};
+Options options_now() {
+    Options opt;
+    for (int i = 0; i < 5; ++i) opt.value[i] = g_options[i].load(std::memory_order_relaxed);
+    return opt;
+}
 
 // Shape checks shared by fa_fwd and fa_fwd_plan; everything here runs before any HIP call.
 int check_shape(int B, int H, int Nq, int Nk, int D, int dtype) {
@@ -212,7 +221,7 @@ int check_shape(int B, int H, int Nq, int Nk, int D, int dtype) {
 
 // One query row per head goes through the streaming kernel (FA_OPT_DECODE_KERNEL = 1 keeps the tile kernel:
 // tests, tuning)
-bool use_streaming_decode(int Nq) { return Nq == 1 && option(FA_OPT_DECODE_KERNEL) != 1; }
+bool use_streaming_decode(const Options &opt, int Nq) { return Nq == 1 && opt[FA_OPT_DECODE_KERNEL] != 1; }
 
 // Work decomposition for a problem: the mode, and the query rows of a workgroup (256, or 128 in FA_MODE_SPLIT and in
 // FA_MODE_WIDE on workgroups of four waves).  W = B * H * ceil(Nq / 256), blocks = B * H * ceil(Nq / 128); the chip has 256
@@ -262,8 +271,7 @@ struct Decomposition {
     int mode, rows;
     bool two_sums = false;       // fp16 on eight waves: both row sums (the four-wave kernels always carry both)
 };
-Decomposition choose_form(int B, int H, int Nq, int Nk, int D, int causal, int dtype) {
-    const int forced = option(FA_OPT_FWD_MODE);
+Decomposition choose_form(int forced, int B, int H, int Nq, int Nk, int D, int causal, int dtype) {
     const Decomposition split = {FA_MODE_SPLIT, 128}, wide = {FA_MODE_WIDE, 256}, four = {FA_MODE_WIDE, 128},
                         fold = {FA_MODE_WIDE_FOLD, 256}, wide64 = {FA_MODE_WIDE64, 256};
     const long long heads = (long long)B * H, blocks = heads * (((long long)Nq + 127) / 128);
@@ -328,9 +336,9 @@ bool fp16_two_sums(int B, int H, int Nq, int Nk, int D, int causal) {
     return causal ? avg_keys < 8192 : !(Nk >= 1536 && (full_rounds || W >= 6 * 256));
 }
 
-Decomposition choose_mode(int B, int H, int Nq, int Nk, int D, int causal, int dtype) {
-    Decomposition d = choose_form(B, H, Nq, Nk, D, causal, dtype);
-    d.two_sums = option(FA_OPT_FWD_MODE) == FA_AUTO && fp16_two_sums(B, H, Nq, Nk, D, causal);
+Decomposition choose_mode(const Options &opt, int B, int H, int Nq, int Nk, int D, int causal, int dtype) {
+    Decomposition d = choose_form(opt[FA_OPT_FWD_MODE], B, H, Nq, Nk, D, causal, dtype);
+    d.two_sums = opt[FA_OPT_FWD_MODE] == FA_AUTO && fp16_two_sums(B, H, Nq, Nk, D, causal);
     return d;
 }
 
@@ -344,8 +352,7 @@ Decomposition choose_mode(int B, int H, int Nq, int Nk, int D, int causal, int d
 // (1.5 rounds of 512) 351 358, 521 540; 1 x 20 x 12000 548 522, 736 716; window 4096 of 2 x 16 x 16384 545 542, 919 912;
 // 8192 of 1 x 16 x 16384 465 478, 711 740; half a round, 1 x 2 x 16384, 247 179, 325 249.  fa_set_option(FA_OPT_FWD_MODE,
 // FA_MODE_WIDE | FA_MODE_WIDE4) overrides (tests, tuning).
-int masked_rows(const MaskGeom &g, long long heads, int Nq, int Nk, int D) {
-    const int forced = option(FA_OPT_FWD_MODE);
+int masked_rows(int forced, const MaskGeom &g, long long heads, int Nq, int Nk, int D) {
     if (forced == FA_MODE_WIDE) return 256;
     if (forced == FA_MODE_WIDE4) return 128;
     const long long W = heads * (((long long)Nq + 255) / 256);
@@ -567,10 +574,10 @@ struct LinearTile {
 // themselves, then leave it a quarter of the chip at least (D = 64, blocks of 1024 whose first has 512 rows: 1 x 20 x 2178,
 // 3840 outputs, 240 of them 100 us, 120 of 128 x 128 95; 1 x 32 x 2093, 3584: 224 117, 112 111; 2 x 40 x 1031, 2560 in
 // blocks of 512, 160 for the first 256 rows: 106, 111). FA_OPT_LINEAR_TILE overrides (tests, tuning).
-LinearTile choose_linear_tile(int B, int rows, int N, bool shared) {
+LinearTile choose_linear_tile(int forced, int B, int rows, int N, bool shared) {
     const LinearTile forms[] = {{64, 128}, {128, 128}, {128, 256}, {256, 256}};
     auto tiles = [&](const LinearTile &t) { return (long long)B * (((long long)rows + t.rows - 1) / t.rows) * (N / t.cols); };
-    switch (option(FA_OPT_LINEAR_TILE)) {
+    switch (forced) {
         case 256: return forms[3];
         case 128: return forms[2];
         case 128128: return forms[1];
@@ -663,7 +670,8 @@ int fa_fwd_plan(int B, int H, int Nq, int Nk, int D, int causal, int dtype, fa_p
     const int rc = check_shape(B, H, Nq, Nk, D, dtype);
     if (rc != FA_OK) return rc;
     const long long tiles_k = ((long long)Nk + BN - 1) / BN;
-    if (use_streaming_decode(Nq)) {
+    const Options opt = options_now();
+    if (use_streaming_decode(opt, Nq)) {
         // one query per head (it sees every key, causal or not): fa_decode_kernel, one workgroup per (batch, head)
         plan->mode = FA_MODE_STREAM;
         plan->block_m = 1;
@@ -675,7 +683,7 @@ int fa_fwd_plan(int B, int H, int Nq, int Nk, int D, int causal, int dtype, fa_p
         plan->lds_bytes = DECODE_WAVES * (512 / D) * (D + 2) * 4;     // one partial state per lane group
         return FA_OK;
     }
-    const Decomposition dec = choose_mode(B, H, Nq, Nk, D, causal, dtype);
+    const Decomposition dec = choose_mode(opt, B, H, Nq, Nk, D, causal, dtype);
     const int mode = dec.mode, BM = dec.rows;
     const bool four = BM == 128 && mode != FA_MODE_SPLIT;
     const long long nqt = ((long long)Nq + BM - 1) / BM;
@@ -695,8 +703,8 @@ int fa_fwd_plan(int B, int H, int Nq, int Nk, int D, int causal, int dtype, fa_p
     return FA_OK;
 }
 
-int fa_fwd(const void *q, const void *k, const void *v, void *o, float *lse, int B, int H, int Nq, int Nk,
-           int D, float scale, int causal, int dtype, void *stream) {
+static int fwd(const Options &opt, const void *q, const void *k, const void *v, void *o, float *lse, int B, int H, int Nq, int Nk,
+               int D, float scale, int causal, int dtype, void *stream) {
     if (!q || !k || !v || !o || !lse) return FA_ERR_NULL;
     const int rc = check_shape(B, H, Nq, Nk, D, dtype);
     if (rc != FA_OK) return rc;
@@ -704,8 +712,8 @@ int fa_fwd(const void *q, const void *k, const void *v, void *o, float *lse, int
     if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o) & 15) return FA_ERR_ALIGN;
     if ((uintptr_t)lse & 3) return FA_ERR_ALIGN;
 
-    const bool stream_kernel = use_streaming_decode(Nq);
-    const Decomposition dec = stream_kernel ? Decomposition{FA_MODE_STREAM, 256} : choose_mode(B, H, Nq, Nk, D, causal, dtype);
+    const bool stream_kernel = use_streaming_decode(opt, Nq);
+    const Decomposition dec = stream_kernel ? Decomposition{FA_MODE_STREAM, 256} : choose_mode(opt, B, H, Nq, Nk, D, causal, dtype);
     const int BM = dec.rows;
     const long long nqt = ((long long)Nq + BM - 1) / BM;
     const long long nwork = (long long)B * H * nqt;
@@ -733,16 +741,20 @@ int fa_fwd(const void *q, const void *k, const void *v, void *o, float *lse, int
     return FA_OK;
 }
 
-int fa_fwd_splitkv_plan(int B, int H, int Nq, int Nk, int D, int causal, int dtype, int nsplit,
-                        fa_splitkv_plan_t *plan) {
-    (void)causal;
+int fa_fwd(const void *q, const void *k, const void *v, void *o, float *lse, int B, int H, int Nq, int Nk,
+           int D, float scale, int causal, int dtype, void *stream) {
+    return fwd(options_now(), q, k, v, o, lse, B, H, Nq, Nk, D, scale, causal, dtype, stream);
+}
+
+// (causal or not, the plan is the same)
+static int splitkv_plan(const Options &opt, int B, int H, int Nq, int Nk, int D, int dtype, int nsplit, fa_splitkv_plan_t *plan) {
     if (!plan) return FA_ERR_NULL;
     const int rc = check_shape(B, H, Nq, Nk, D, dtype);
     if (rc != FA_OK) return rc;
     if (nsplit > SPLITKV_MAX) return FA_ERR_NSPLIT;
     const long long nqt = ((long long)Nq + 255) / 256;
     const long long nwork = (long long)B * H * nqt;
-    const bool streaming = use_streaming_decode(Nq);
+    const bool streaming = use_streaming_decode(opt, Nq);
     const SplitChoice choice = choose_nsplit(B, H, Nq, Nk, D, nsplit, streaming);
     const int ns = choice.nsplit;
     const long long rows = (long long)B * H * Nq;
@@ -757,12 +769,18 @@ int fa_fwd_splitkv_plan(int B, int H, int Nq, int Nk, int D, int causal, int dty
     return FA_OK;
 }
 
-int fa_fwd_splitkv(const void *q, const void *k, const void *v, void *o, float *lse, int B, int H, int Nq, int Nk,
-                   int D, float scale, int causal, int dtype, int nsplit, void *workspace, long long workspace_bytes,
+int fa_fwd_splitkv_plan(int B, int H, int Nq, int Nk, int D, int causal, int dtype, int nsplit,
+                        fa_splitkv_plan_t *plan) {
+    (void)causal;
+    return splitkv_plan(options_now(), B, H, Nq, Nk, D, dtype, nsplit, plan);
+}
+
+static int splitkv(const Options &opt, const void *q, const void *k, const void *v, void *o, float *lse, int B, int H, int Nq,
+                   int Nk, int D, float scale, int causal, int dtype, int nsplit, void *workspace, long long workspace_bytes,
                    void *stream) {
     if (!q || !k || !v || !o || !lse) return FA_ERR_NULL;
     fa_splitkv_plan_t pl;
-    const int rc = fa_fwd_splitkv_plan(B, H, Nq, Nk, D, causal, dtype, nsplit, &pl);
+    const int rc = splitkv_plan(opt, B, H, Nq, Nk, D, dtype, nsplit, &pl);
     if (rc != FA_OK) return rc;
     if (!isfinite(scale)) return FA_ERR_SCALE;
     if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o) & 15) return FA_ERR_ALIGN;
@@ -773,7 +791,7 @@ int fa_fwd_splitkv(const void *q, const void *k, const void *v, void *o, float *
     if (rows > 0x7fffffffLL * 8) return FA_ERR_SHAPE;   // combine grid
     // a single run has nothing to merge: it is fa_fwd's launch (whose decompositions beat a one-run walk of
     // the split-KV kernel by about 5% when there are enough query blocks to fill the chip without splitting)
-    if (pl.nsplit == 1) return fa_fwd(q, k, v, o, lse, B, H, Nq, Nk, D, scale, causal, dtype, stream);
+    if (pl.nsplit == 1) return fwd(opt, q, k, v, o, lse, B, H, Nq, Nk, D, scale, causal, dtype, stream);
 
     FaParams p = base_params(q, k, v, o, lse, H, Nq, Nk, ((long long)Nq + 255) / 256, pl.work_items, scale);
     p.nsplit = pl.nsplit;
@@ -801,7 +819,7 @@ int fa_fwd_splitkv(const void *q, const void *k, const void *v, void *o, float *
     }
     // keys a query sees per run, on average (as in choose_mode): from 4096 the wide64 kernel is the faster one
     const long long avg_keys = causal ? (long long)Nk - Nq / 2 : (long long)Nk;
-    const bool long_runs = D == 128 && !p.kv_stream && option(FA_OPT_FWD_MODE) != FA_MODE_WIDE &&
+    const bool long_runs = D == 128 && !p.kv_stream && opt[FA_OPT_FWD_MODE] != FA_MODE_WIDE &&
                            avg_keys / pl.nsplit >= 4096;
     const int key = (dtype << 2) | ((D == 128) << 1) | (causal ? 1 : 0);
     switch (key) {
@@ -822,17 +840,24 @@ int fa_fwd_splitkv(const void *q, const void *k, const void *v, void *o, float *
     return FA_OK;
 }
 
+int fa_fwd_splitkv(const void *q, const void *k, const void *v, void *o, float *lse, int B, int H, int Nq, int Nk,
+                   int D, float scale, int causal, int dtype, int nsplit, void *workspace, long long workspace_bytes,
+                   void *stream) {
+    return splitkv(options_now(), q, k, v, o, lse, B, H, Nq, Nk, D, scale, causal, dtype, nsplit, workspace, workspace_bytes, stream);
+}
+
 int fa_fwd_splitkv_static(const void *q, const void *k, const void *v, void *o, float *lse, int B, int H, int Nq,
                           int Nk, int D, float scale, int causal, int dtype, int nsplit, void *stream) {
+    const Options opt = options_now();
     // every argument check first (no HIP call before them), the size limit among them
     if (!q || !k || !v || !o || !lse) return FA_ERR_NULL;
     fa_splitkv_plan_t pl;
-    const int rc = fa_fwd_splitkv_plan(B, H, Nq, Nk, D, causal, dtype, nsplit, &pl);
+    const int rc = splitkv_plan(opt, B, H, Nq, Nk, D, dtype, nsplit, &pl);
     if (rc != FA_OK) return rc;
     if (!isfinite(scale)) return FA_ERR_SCALE;
     if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o) & 15) return FA_ERR_ALIGN;
     if ((uintptr_t)lse & 3) return FA_ERR_ALIGN;
-    if (pl.nsplit == 1) return fa_fwd(q, k, v, o, lse, B, H, Nq, Nk, D, scale, causal, dtype, stream);   // nothing to merge
+    if (pl.nsplit == 1) return fwd(opt, q, k, v, o, lse, B, H, Nq, Nk, D, scale, causal, dtype, stream);   // nothing to merge
     if (pl.workspace_bytes > FA_STATIC_WORKSPACE_BYTES) return FA_ERR_WORKSPACE;
     void *ws = nullptr;
     {
@@ -858,8 +883,7 @@ int fa_fwd_splitkv_static(const void *q, const void *k, const void *v, void *o, 
             return FA_ERR_LAUNCH;
         }
     }
-    return fa_fwd_splitkv(q, k, v, o, lse, B, H, Nq, Nk, D, scale, causal, dtype, nsplit, ws, FA_STATIC_WORKSPACE_BYTES,
-                          stream);
+    return splitkv(opt, q, k, v, o, lse, B, H, Nq, Nk, D, scale, causal, dtype, nsplit, ws, FA_STATIC_WORKSPACE_BYTES, stream);
 }
 
 int fa_fwd_masked(const void *q, const void *k, const void *v, void *o, float *lse, int B, int H, int Nq, int Nk,
@@ -874,7 +898,8 @@ int fa_fwd_masked(const void *q, const void *k, const void *v, void *o, float *l
     if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o) & 15) return FA_ERR_ALIGN;
     if (((uintptr_t)lse | (uintptr_t)mask->kv_len) & 3) return FA_ERR_ALIGN;
 
-    const int rows = masked_rows(g, (long long)B * H, Nq, Nk, D);
+    const Options opt = options_now();
+    const int rows = masked_rows(opt[FA_OPT_FWD_MODE], g, (long long)B * H, Nq, Nk, D);
     const long long nqt = ((long long)Nq + rows - 1) / rows;
     const long long nwork = (long long)B * H * nqt;
     FaParams p = base_params(q, k, v, o, lse, H, Nq, Nk, nqt, nwork, scale);
@@ -886,7 +911,7 @@ int fa_fwd_masked(const void *q, const void *k, const void *v, void *o, float *l
     const int grid = p.per_xcd * 8;
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
-    if (use_streaming_decode(Nq)) {
+    if (use_streaming_decode(opt, Nq)) {
         // one query per head: the streaming kernel walks the prefix and the window as runs of consecutive keys
         switch ((dtype << 1) | (D == 128)) {
             case 0: e = launch_decode_masked<0, 64>(p, (int)nwork, st); break;
@@ -918,7 +943,7 @@ int fa_decode_masked(const void *q, const void *k, const void *v, void *o, float
                      long long workspace_bytes, void *stream) {
     if (!q || !k || !v || !o || !lse || !mask) return FA_ERR_NULL;
     fa_splitkv_plan_t pl;
-    const int rc = fa_fwd_splitkv_plan(B, H, 1, Nk, D, 0, dtype, nsplit, &pl);
+    const int rc = splitkv_plan(options_now(), B, H, 1, Nk, D, dtype, nsplit, &pl);
     if (rc != FA_OK) return rc;
     if (!isfinite(scale)) return FA_ERR_SCALE;
     MaskGeom g;
@@ -979,12 +1004,12 @@ int check_attn_linear(const void *q, const void *k, const void *v, const void *w
 
 // attention of one block of rows, every head: a launch over row_count rows whose diagonal is shifted by
 // row_first; q, o, lse keep the full tensors' head pitch.  Arguments already checked.
-int block_attention(const void *q, const void *k, const void *v, void *o, float *lse, int B, int H, int Nq, int Nk,
+int block_attention(const Options &opt, const void *q, const void *k, const void *v, void *o, float *lse, int B, int H, int Nq, int Nk,
                     int D, float scale, int causal, int dtype, int row_first, int row_count, hipStream_t st) {
     {
         // (the keys the block's rows can see end at its last row's diagonal)
         const int nk_seen = causal ? Nk - (Nq - row_first - row_count) : Nk;
-        const Decomposition dec = choose_mode(B, H, row_count, nk_seen > 0 ? nk_seen : 1, D, causal, dtype);
+        const Decomposition dec = choose_mode(opt, B, H, row_count, nk_seen > 0 ? nk_seen : 1, D, causal, dtype);
         const int BM = dec.rows;
         const long long nqt = ((long long)row_count + BM - 1) / BM;
         const long long nwork = (long long)B * H * nqt;
@@ -1002,7 +1027,7 @@ int block_attention(const void *q, const void *k, const void *v, void *o, float 
 }
 
 // the block's rows of y = (heads side by side) x w; `shared`: beside the next block's attention.  Arguments already checked.
-int block_projection(const void *w, const void *o, float *y, int B, int H, int Nq, int D, int N, int dtype,
+int block_projection(const Options &opt, const void *w, const void *o, float *y, int B, int H, int Nq, int D, int N, int dtype,
                      int row_first, int row_count, bool shared, hipStream_t st) {
     {
         LinParams lp;
@@ -1015,7 +1040,7 @@ int block_projection(const void *w, const void *o, float *y, int B, int H, int N
         lp.s0 = row_first;
         lp.rows = row_count;
         lp.d_shift = D == 128 ? 7 : 6;
-        const LinearTile t = choose_linear_tile(B, row_count, N, shared);
+        const LinearTile t = choose_linear_tile(opt[FA_OPT_LINEAR_TILE], B, row_count, N, shared);
         lp.n_tiles = N / t.cols;
         lp.mt_per_b = (row_count + t.rows - 1) / t.rows;
         const long long tiles = (long long)B * lp.mt_per_b * lp.n_tiles;
@@ -1023,7 +1048,7 @@ int block_projection(const void *w, const void *o, float *y, int B, int H, int N
         lp.ntile_total = (int)tiles;
         lp.per_xcd = (int)((tiles + 7) / 8);
         lp.panel = linear_panel(lp.per_xcd, t, B * lp.mt_per_b);
-        if (const int v = option(FA_OPT_LINEAR_PANEL); v >= 1)   // tests, tuning
+        if (const int v = opt[FA_OPT_LINEAR_PANEL]; v >= 1)   // tests, tuning
             lp.panel = v < B * lp.mt_per_b ? v : B * lp.mt_per_b;
         const hipError_t e = dtype == FA_DTYPE_F16 ? launch_linear<0>(lp, t, st) : launch_linear<1>(lp, t, st);
         if (e != hipSuccess) {
@@ -1052,10 +1077,11 @@ int fa_attn_linear_block(const void *q, const void *k, const void *v, const void
                          int row_first, int row_count, void *stream) {
     int rc = check_attn_linear(q, k, v, w, o, lse, y, B, H, Nq, Nk, D, N, scale, dtype, row_first, row_count);
     if (rc != FA_OK) return rc;
+    const Options opt = options_now();
     hipStream_t st = (hipStream_t)stream;
-    rc = block_attention(q, k, v, o, lse, B, H, Nq, Nk, D, scale, causal, dtype, row_first, row_count, st);
+    rc = block_attention(opt, q, k, v, o, lse, B, H, Nq, Nk, D, scale, causal, dtype, row_first, row_count, st);
     if (rc != FA_OK) return rc;
-    return block_projection(w, o, y, B, H, Nq, D, N, dtype, row_first, row_count, false, st);
+    return block_projection(opt, w, o, y, B, H, Nq, D, N, dtype, row_first, row_count, false, st);
 }
 
 int fa_attn_linear(const void *q, const void *k, const void *v, const void *w, void *o, float *lse, float *y, int B,
@@ -1065,6 +1091,7 @@ int fa_attn_linear(const void *q, const void *k, const void *v, const void *w, v
         return fa_attn_linear_block(q, k, v, w, o, lse, y, B, H, Nq, Nk, D, N, scale, causal, dtype, 0, Nq, stream);
     int rc = check_attn_linear(q, k, v, w, o, lse, y, B, H, Nq, Nk, D, N, scale, dtype, 0, Nq);
     if (rc != FA_OK) return rc;
+    const Options opt = options_now();
     hipStream_t st = (hipStream_t)stream;
 
     // The projection of block i and the attention of block i + 1 touch different rows, so the projections go to
@@ -1074,7 +1101,7 @@ int fa_attn_linear(const void *q, const void *k, const void *v, const void *w, v
     // behaves as if everything had been enqueued on `stream`.
     SideStream *side = nullptr;
     std::unique_lock<std::mutex> hold;
-    if (option(FA_OPT_LINEAR_OVERLAP) != 0) {
+    if (opt[FA_OPT_LINEAR_OVERLAP] != 0) {
         int dev = 0;
         hipError_t e = hipGetDevice(&dev);
         if (e != hipSuccess || dev < 0 || dev >= 64) {
@@ -1110,7 +1137,7 @@ int fa_attn_linear(const void *q, const void *k, const void *v, const void *w, v
     bool forked = false;
     for (int r = 0; r < Nq && rc == FA_OK;) {
         const int n = r == 0 ? first : (Nq - r < rows_per_block ? Nq - r : rows_per_block);
-        rc = block_attention(q, k, v, o, lse, B, H, Nq, Nk, D, scale, causal, dtype, r, n, st);
+        rc = block_attention(opt, q, k, v, o, lse, B, H, Nq, Nk, D, scale, causal, dtype, r, n, st);
         if (rc != FA_OK) break;
         hipStream_t lin_stream = st;
         if (side) {
@@ -1124,7 +1151,7 @@ int fa_attn_linear(const void *q, const void *k, const void *v, const void *w, v
             forked = true;
             lin_stream = side->stream;
         }
-        rc = block_projection(w, o, y, B, H, Nq, D, N, dtype, r, n, side && Nq - r - n >= n / 2, lin_stream);
+        rc = block_projection(opt, w, o, y, B, H, Nq, D, N, dtype, r, n, side && Nq - r - n >= n / 2, lin_stream);
         r += n;
     }
     if (forked) {      // also after an error: the second stream must rejoin (a capture could not end otherwise)

@@ -160,6 +160,26 @@ def test_bench_libraries_export_what_their_header_declares_and_the_product_libra
     assert g.fa_mfma_probe(0, 1, 10, 0x1002, ctypes.byref(f), None) == -6
 
 
+def test_every_call_reads_the_options_once():
+    """A change made from another thread while a call is under way applies to the next call: each entry point takes a copy of the
+    options, once, and nothing below it reads them."""
+    with open(os.path.join(ROOT, "paper_2410_16663_amd", "csrc", "fa_fwd.hip")) as f:
+        src = re.sub(r"//.*", "", f.read())
+    bodies = dict(re.findall(r"^(?:[\w:<>*]+ )+\*?(\w+)\([^;{]*\{\n(.*?)^\}", src, flags=re.M | re.S))
+    readers = {name for name, body in bodies.items() if "g_options[" in body}
+    assert readers == {"options_now", "fa_set_option"}
+    assert set(ENTRY_POINTS_WITH_OPTIONS) <= set(bodies)
+    for name, body in bodies.items():
+        assert body.count("options_now()") == (1 if name in ENTRY_POINTS_WITH_OPTIONS else 0), name
+        # an entry point that calls another before its own copy is taken leaves the reading to it
+        calls = [e for e in ENTRY_POINTS_WITH_OPTIONS if re.search(rf"\b{e}\(", body)]
+        assert not calls or (name, calls) == ("fa_attn_linear", ["fa_attn_linear_block"]), (name, calls)
+
+
+ENTRY_POINTS_WITH_OPTIONS = ("fa_fwd", "fa_fwd_plan", "fa_fwd_splitkv", "fa_fwd_splitkv_plan", "fa_fwd_splitkv_static", "fa_fwd_masked",
+                             "fa_decode_masked", "fa_attn_linear", "fa_attn_linear_block")
+
+
 def test_options_take_only_their_values_and_return_the_previous_one(lib):
     assert fa.fa_set_option(fa.FA_OPT_FWD_MODE, fa.FA_MODE_WIDE) == fa.FA_AUTO
     assert fa.fa_set_option(fa.FA_OPT_FWD_MODE, fa.FA_MODE_SPLIT) == fa.FA_MODE_WIDE

@@ -3,7 +3,7 @@
 
 A step is one fa_fwd launch over one batch of synthetic input already resident in HBM.
 Prints ONE JSON line: whole-job TFLOP/s on the headline workload -- C5, the long-context causal
-configuration (B=1, H=32, N=131072, D=128, bf16), the largest of the benchmark's configurations and the
+configuration (B=1, H=32, N=131072, D=128, bf16), the largest of the named configurations and the
 one the ">= 50% of MFMA peak on the causal long-sequence configurations" target is about -- with the
 roofline figures of the kernel measured with HIP events on the launch stream, the output of the timed
 launches checked against the CPU oracle (every element for C1/C2, the seeded sample of 64 rows per head
@@ -180,7 +180,7 @@ def decode_entry(I, torch, fa, steps, warmup):
             "roofline": {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": round(gbs / HBM_PEAK_GBS, 4), **traffic_fields("splitkv_DEC"),
                          "kernel": ("fa_decode_kernel" if plan.streaming else "fa_fwd_kernel (wide, split-KV)")
-                                   + " + fa_combine_kernel",
+                                   + (" + fa_combine_kernel" if plan.combine_grid else ""),
                          "bytes_per_call": kv_bytes}}
 
 

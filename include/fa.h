@@ -90,8 +90,8 @@ int fa_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
  * WIDE_FOLD for causal triangles (Nk little over Nq) of up to four rounds whose last one is not nearly empty and for blocks
  * of rows on long caches of 1.65 to two rounds; SPLIT for triangles of 1 to 1.5 rounds or little over two, for such blocks of
  * rows below 1.65 rounds, for other triangles over 2200 keys on average in up to 7.4 rounds, and for full attention over 1000
- * keys and more in 1 to 1.6 rounds, over 1535 in 2 to 2.5.  Else WIDE, on 256 rows for long
- * walks (full: 1536 keys, at D = 64 in bf16 850; causal at D = 64: over 4096) and on 128 otherwise.
+ * keys and more in 1 to 1.6 rounds, over 1535 in 2 to 2.5 (below 3000 only if the rounds of 128-row blocks are filled).  Else
+ * WIDE, on 256 rows for long walks (full: 1536 keys, at D = 64 in bf16 850; causal at D = 64: over 4096) and on 128 otherwise.
  * fa_set_option(FA_OPT_FWD_MODE, ...) overrides the choice (tests, tuning).
  * Nq = 1 (one decoding step) takes none of these: FA_MODE_STREAM, the register-streaming kernel
  * described at fa_fwd_splitkv, one workgroup per (batch, head) -- full speed when B*H fills the
@@ -132,7 +132,8 @@ int fa_fwd_plan(int B, int H, int Nq, int Nk, int D, int causal, int dtype, fa_p
  * reference, row sum -- the running quantities of appendix A) in `workspace`, and they are
  * merged: lse = logsumexp over runs, o = sum_runs exp(lse_run - lse) o_run.  A second kernel does that, or, for a
  * single query and at most D/4 runs, the workgroup that finishes a head's last run (it is found through marks the runs leave
- * in the head's row of o, which holds them until the result replaces them; a process-wide counter gives every call a mark of its own).
+ * in the head's row of o, which holds them until the result replaces them; a process-wide counter gives every call a mark of
+ * its own, the only state the library keeps between such calls).
  * Bound by reading K and V once from HBM.  Nq = 1, the decoding step proper, runs a kernel of its
  * own that streams K and V through registers (one multiply-add per element leaves the matrix
  * cores nothing to reuse) and keeps the probabilities in fp32; fa_set_option(FA_OPT_DECODE_KERNEL, 1)

@@ -249,14 +249,14 @@ bool use_streaming_decode(const Options &opt, int Nq) { return Nq == 1 && opt[FA
 //    8192, two and a half rounds: 437, rows 329); from 8192 keys on before the fold (1 x 32 x 2048 on 16384: 440, fold 472;
 //    2 x 32 x 4096 on 12288 fp16: 1230, 1269; 1 x 32 x 2048 on 7168: 207, 202), unless the last of a few blocks is mostly
 //    padding, which the fold spreads over a head's workgroups (80 x 1302 on 16068 fp16: 1020, rows 1047, fold 939).
-//  * a third round of 512 256-row workgroups that would be nearly empty, full attention at D = 64 over 1535 keys: FA_MODE_SPLIT
+//  * a second round of 512 256-row workgroups that would be nearly empty, full attention at D = 64 over 1535 keys: FA_MODE_SPLIT
 //    (wide and split: 9 x 2 x 8712, 2.46 times 256 of them, 436, 391; 13 x 5 x 1896, 2.03, 96, 77; 1 x 20 x 7058, 2.19, 344, 311;
-//    10 x 20 x 599 on 2673, 2.34, 112, 98; with a last round of 128-row workgroups that is as empty, and short walks, not: 10 x 8
-//    x 1587 on 1683, 1040 of them, 79, 81; 2 x 32 x 2119, 1088, 104, 106).
+//    10 x 20 x 599 on 2673, 2.34, 112, 98), unless the last round of 256 128-row workgroups is as empty and the walk below 3000
+//    keys (10 x 8 x 1587 on 1683, 1040 of them, 79, 81; 2 x 32 x 2119, 1088, 104, 106).
 //  * causal triangles at D = 64 over 2200 keys on average in three to seven and a half rounds that are not the fold's: FA_MODE_SPLIT
 //    (over 4096 keys against wide: 12 x 2 x 13340, 5.0 rounds, 696, 631; 2 x 12 x 9332, 3.5, 348, 314; 2 x 12 x 13540 fp16, 5.0, 685,
-//    640; 4 x 12 x 9280, 6.9, 631, 600; 6 x 20 x 4496, 8.4, level; below against four waves: 3 x 12 x 7581 fp16, 4.2, 387, 370; 3 x
-//    20 x 5446, 5.2, 301, 286; 2 x 32 x 6731, 6.75, 486, 475; 10 x 12 x 5019, 9.4, 520, 523).
+//    640; 4 x 12 x 9280, 6.9, 631, 600; below against four waves: 3 x 12 x 7581 fp16, 4.2, 387, 370; 3 x 20 x 5446, 5.2, 301, 286; 2 x
+//    32 x 6731, 6.75, 486, 475; 6 x 20 x 4496, 8.4, level; 10 x 12 x 5019, 9.4, 520, 523).
 //  * everything else on four waves, whose waves share a SIMD with other workgroups' (D = 128 causal: 16 x 32 x 2048 590,
 //    wide 745; 3 x 20 x 1531 47, split 68, wide 70; full: 47 x 32 x 280 122, wide 205), but for full attention over 1536
 //    keys and more (at D = 64 in bf16 and filled rounds 850), where the tiles loaded per 256 rows count (4 x 32 x 2048: wide
@@ -293,7 +293,7 @@ Decomposition choose_form(int forced, int B, int H, int Nq, int Nk, int D, int c
     if (D == 64) {
         if (W >= 256 && Nq > 128 && Nq <= 144 && (!causal || Nk >= Nq + 16)) return wide;
         if (!causal && avg_keys >= 1000 && W > 256 && W <= 404) return split;
-        const bool full_split = (blocks + 255) / 256 * 256 * 100 <= blocks * 116;       // the same for rounds of 256 split workgroups
+        const bool full_split = (blocks + 255) / 256 * 256 * 100 <= blocks * 116;       // rounds of 128-row workgroups, the last 5/6 full
         if (!causal && avg_keys > 1535 && W > 512 && W <= 640 && (full_split || avg_keys >= 3000)) return split;
         if (!causal) return avg_keys > 1535 || (dtype == FA_DTYPE_BF16 && avg_keys >= 850 && (W < 256 || full_rounds)) ? wide : four;
         if (nqt >= 4 && 10ll * Nq >= 7ll * Nk) {

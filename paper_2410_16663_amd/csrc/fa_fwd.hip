@@ -182,9 +182,10 @@ unsigned long long tag_seed() noexcept {
 }
 // Whether fa_decode_kernel merges the runs of a head, `runs` of them at most, by itself: their tags fit into a row of o
 bool merges_itself(int runs, int D) { return runs > 1 && runs <= D / 4; }
-// FaParams::tag of a call that does: 64 bits that no other memory holds by chance.  Every call of the process gets a value of its own, so that what an earlier one
-// left in o is not taken for a mark.  A captured call's value is an argument of its node, the same on every replay: a replay leaves
-// none of its marks behind, because the kernel does not end before every head of several runs has its marks replaced by the result.
+// FaParams::tag of a call that does: 64 bits that no other memory holds by chance.  Every call of the process gets a value of its
+// own, so that what an earlier one left in o is not taken for a mark.  A captured call's value is an argument of its node, the same
+// on every replay: a replay leaves none of its marks behind, because the kernel does not end before every head of several runs has
+// its marks replaced by the result.
 unsigned long long decode_tag() noexcept {
     static std::atomic<unsigned long long> calls{tag_seed()};
     unsigned long long x = calls.fetch_add(0x9e3779b97f4a7c15ull, std::memory_order_relaxed);   // (SplitMix64: a bijection)
@@ -293,7 +294,7 @@ Decomposition choose_form(int forced, int B, int H, int Nq, int Nk, int D, int c
     if (D == 64) {
         if (W >= 256 && Nq > 128 && Nq <= 144 && (!causal || Nk >= Nq + 16)) return wide;
         if (!causal && avg_keys >= 1000 && W > 256 && W <= 404) return split;
-        const bool full_split = (blocks + 255) / 256 * 256 * 100 <= blocks * 116;       // rounds of 128-row workgroups, the last 5/6 full
+        const bool full_split = (blocks + 255) / 256 * 256 * 100 <= blocks * 116;   // rounds of 128-row workgroups, 86% of their places taken
         if (!causal && avg_keys > 1535 && W > 512 && W <= 640 && (full_split || avg_keys >= 3000)) return split;
         if (!causal) return avg_keys > 1535 || (dtype == FA_DTYPE_BF16 && avg_keys >= 850 && (W < 256 || full_rounds)) ? wide : four;
         if (nqt >= 4 && 10ll * Nq >= 7ll * Nk) {

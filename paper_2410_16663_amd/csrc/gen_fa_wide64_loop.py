@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Writes fa_attention_wide64_loop.inc: the check-free main loop of fa_fwd_wide64_kernel as one inline-assembly
-block per storage type -- the software-pipelined form of the attention loop for waves of 64 query rows (two 32-row
-blocks rb = 0, 1 that share every K and V fragment read from LDS).  One wave per SIMD, the whole register file.
+block per storage type -- the software-pipelined form of the attention loop for waves of 64 query rows (four 16-row
+blocks qb = 0 .. 3 that share every K and V fragment read from LDS).  One wave per SIMD, the whole register file.
 
 Why assembly, and why generated: with one wave per SIMD nothing hides a wave's vector work but the wave itself, so
 the instruction stream has to alternate -- one matrix instruction, then about as many vector / LDS / load
@@ -11,29 +11,40 @@ allocator, hence fixed registers and a fixed order; the loop is regular, hence w
 this script (paper_2410_16663_amd/build.py); the .inc file is its output and is not kept under version control.
 
 Register plan (per lane):
-    a0   .. a127   O accumulators, O[rb][db] = a[64*rb + 16*db : +15]        (outputs of the block)
-    a128 .. a191   Q fragments,    Q[rb][kb] = a[128 + 32*rb + 4*kb : +3]    (inputs)
-    v0   .. v127   four unit buffers x two row blocks, X[b][rb] = v[32*b + 16*rb : +15]: unit u lives in X[u % 4],
-                   first as logits, then (overwritten in place) as packed exponentials P[jj] = first 4 registers of
-                   each half
+    a0   .. a127   O accumulators, O[qb][db] = a[32*qb + 4*db : +3]          (outputs of the block)
+    a128 .. a191   Q fragments,    Q[qb][kb] = a[128 + 16*qb + 4*kb : +3]    (inputs)
+    a192 .. a207   sums of the rounded exponentials, L[qb] = a[192 + 4*qb : +3], a row of the second product with ones
+                   for V^T (all four registers the same; outputs)
+    v0   .. v127   four unit buffers x four row blocks, X[b][qb] = v[32*b + 8*qb : +7]: unit u lives in X[u % 4], first
+                   as logits (key block mb in registers 4*mb .. +3), then (overwritten in place) as packed exponentials
+                   P = its first 4 registers
     v128 .. v143   four K fragments in flight;   v144 .. v159   four V^T fragments in flight
-    v160+rb m_ref, v162+rb l_run, v164+rb l_rnd                               (outputs)
-    v166, v167     K fragment address, even (input) / odd k-step
-    v168 .. v171   V^T fragment address per 32-row block of O^T (v168 input)
-    v172, v173     per-lane byte offsets of the K and V loads from global memory (inputs)
-    v174 .. v185   temporaries, six per row block;   v186 .. v193   per-lane offsets of the four loads per tensor
-Scalar registers s60 .. s69 are scratch of the block.
+    v160+qb m_ref, v164+qb l_run (bf16: sum of the unrounded exponentials)    (outputs)
+    v168 .. v171   the fragment of ones
+    v172           K fragment address (input);   v173 .. v180   V^T fragment address per 16-row block of O^T (v173 input)
+    v181, v182     per-lane byte offsets of the K and V loads from global memory (inputs)
+    v183 .. v186   per row block of a unit: the sum of its exponentials (fp16: the largest)
+    v191, v192     temporaries;   v193 .. v200   per-lane offsets of the four loads per tensor
+Scalar registers s60 .. s67 are scratch of the block.
 
 A UNIT is 32 keys x the wave's 64 rows.  In step u the wave issues
-    the 16 matrix instructions of unit u+1's logits   S(u+1) = K Q^T,
-    the 16 matrix instructions of unit u-1's second product   O += V^T P(u-1),
-    and BETWEEN them the ~150 vector instructions of unit u's softmax   S(u) -> P(u)   (both row blocks), the
-    LDS reads of the fragments three matrix-instruction pairs ahead, and this wave's share of a tile's loads,
-each matrix instruction followed by at most CAP cycles' worth of the others (by a simple cost table; the best CAP
-was found by timing).  The test "row sum <= 256" (which proves that no exponential exceeded 256, see the kernel)
-is computed at the end of the step's vector work and branched on after its last matrix instruction; the rare other
-case runs a block out of line that recomputes the unit's logits, takes the row maxima, moves the references,
-rescales the accumulators (through v_accvgpr_read / write) and redoes the exponentials.
+    the 32 matrix instructions of unit u+1's logits   S(u+1) = K Q^T,
+    the 32 matrix instructions of unit u-1's second product   O += V^T P(u-1), and 4 for its row of ones,
+    and BETWEEN them the ~140 vector instructions of unit u's softmax   S(u) -> P(u)   (all row blocks), the
+    LDS reads of the fragments three groups of four matrix instructions ahead, and this wave's share of a tile's loads.
+The test "row sum <= 256" (which proves that no exponential exceeded 256, see the kernel) is computed at the end of the
+step's vector work and branched on after its last matrix instruction; the rare other case runs a block out of line that
+recomputes the unit's logits, takes the row maxima, moves the references, rescales the accumulators (through
+v_accvgpr_read / write) and redoes the exponentials.
+
+What issues when (measured, cycles, one wave per SIMD, all operands in registers): a 16 x 16 x 32 matrix instruction occupies
+the matrix pipe for 16 and the vector port for 8 of them, so two vector instructions (4 each) or one v_exp_f32 (8) fit
+behind it: 17.0 with two additions, 21.0 with three, 25.0 with four, 21.0 with v_fma and v_exp; a 32 x 32 x 16 (32) takes
+six (33.0; eight: 41.0).  In the last 4 cycles of its port time something that is no vector instruction may issue (three
+s_nop behind one: 17.0).  Four matrix instructions in a row, then eight additions: 89 instead of 68.  A dot product shares
+the matrix pipe and stops it: 33.0 with one behind each matrix instruction, which is why no sum is taken with v_dot2c.
+So each matrix instruction is followed by at most one LDS read or load instruction and by as many vector instructions as
+are its even share of the step's, CAP cycles at least.
 
 LDS: four stages of (K tile, V tile); tile t lives in stage t % 4.  Barrier k (the k-th of the walk, the same count
 as in the compiler-scheduled loop around this block) publishes tile k+1 and certifies that no wave reads tile k-1
@@ -43,46 +54,52 @@ Steps: the block computes S(0), runs step 0 (no second product yet), then the st
 so that buffers and stages come round to where they started -- and leaves after step 2J-1 (J = number of tiles, even)
 through one of two exits, each followed by the second product of the last unit.
 
+Matrix instructions are 16 x 16 x 32: under the power limit the same flop cost less than as 32 x 32 x 16 (see mfma16 in
+fa_device.inc), which pays for twice as many issue slots.  Four in a row share their K or V^T fragment, and neighbouring
+groups run through the row blocks in opposite directions, so that consecutive ones mostly share an operand.
+
 Hazards the hardware does not interlock, spaced by hand: 11 wait states between a matrix instruction and a vector
 instruction touching its result (here: always a whole step apart, except in the blocks out of line, which wait);
-results of v_exp_f32 are consumed several instructions later; 3 wait states between a dot-product instruction and
-another kind of instruction reading its result, 2 between v_cvt_pk and the dot product reading it; 2 around
-v_permlane32_swap.
+results of v_exp_f32 are consumed several instructions later; 2 wait states around v_permlane32_swap.
 """
 import os
 
-KB, DB = 8, 4
+KB, DB = 4, 8
 KBLK = 1088
 KTILEB = 16 * KBLK      # 17408
 TILEB = 16384
 NSTAGE = 4
-CAP = 30                # cycles of other instructions issued behind a matrix instruction (measured best of 22..60)
+QB, MB = 4, 2            # 16-row blocks of a wave, 16-key blocks of a unit
+CAP = 8                 # cycles of vector instructions issued behind a matrix instruction (4: 1.00, 12: 0.98 of the speed)
 NW = 4                  # waves per workgroup
 NI = 16 // NW           # load instructions per wave, tensor and tile
 
 
-def O(rb, db):
-    r = 64 * rb + 16 * db
-    return f"a[{r}:{r + 15}]"
-
-
-def Q(rb, kb):
-    r = 128 + 32 * rb + 4 * kb
+def O(qb, db):
+    r = 32 * qb + 4 * db
     return f"a[{r}:{r + 3}]"
 
 
-def X(b, rb):
-    r = 32 * b + 16 * rb
-    return f"v[{r}:{r + 15}]"
+def Q(qb, kb):
+    r = 128 + 16 * qb + 4 * kb
+    return f"a[{r}:{r + 3}]"
 
 
-def x(b, rb, i):
-    return f"v{32 * b + 16 * rb + i}"
+def LSUM(qb):
+    return f"a[{192 + 4 * qb}:{192 + 4 * qb + 3}]"
 
 
-def P(b, rb, jj):
-    r = 32 * b + 16 * rb + 8 * jj
+def X(b, qb, mb):
+    r = 32 * b + 8 * qb + 4 * mb
     return f"v[{r}:{r + 3}]"
+
+
+def x(b, qb, i):
+    return f"v{32 * b + 8 * qb + i}"
+
+
+def P(b, qb):
+    return X(b, qb, 0)
 
 
 def KF(b):
@@ -101,23 +118,22 @@ def VFhi(b):
     return f"v[{144 + 4 * b + 2}:{144 + 4 * b + 3}]"
 
 
-M_REF = lambda rb: f"v{160 + rb}"
-L_RUN = lambda rb: f"v{162 + rb}"
-L_RND = lambda rb: f"v{164 + rb}"
-KADDR = lambda odd: f"v{166 + odd}"
-VADDR = lambda db: f"v{168 + db}"
-KVOFF, VVOFF = "v172", "v173"
-T = lambda rb, i: f"v{174 + 6 * rb + i}"
-DMAOFF = lambda tensor, n: f"v{186 + 4 * tensor + n}"     # per-lane byte offset of load n of a K / V tile
+M_REF = lambda qb: f"v{160 + qb}"
+L_RUN = lambda qb: f"v{164 + qb}"
+ONES = "v[168:171]"
+KADDR = "v172"
+VADDR = lambda db: f"v{173 + db}"
+KVOFF, VVOFF = "v181", "v182"
+SUM = lambda qb: f"v{183 + qb}"              # of a unit's exponentials (fp16: the largest)
+T4, T5 = "v191", "v192"
+DMAOFF = lambda tensor, n: f"v{193 + 4 * tensor + n}"     # per-lane byte offset of load n of a K / V tile
 
 
 class Gen:
     def __init__(self, bf16):
         self.bf16 = bf16
-        self.mfma = "v_mfma_f32_32x32x16_bf16" if bf16 else "v_mfma_f32_32x32x16_f16"
+        self.mfma = "v_mfma_f32_16x16x32_bf16" if bf16 else "v_mfma_f32_16x16x32_f16"
         self.cvt = "v_cvt_pk_bf16_f32" if bf16 else "v_cvt_pk_f16_f32"
-        self.dot = "v_dot2c_f32_bf16_e32" if bf16 else "v_dot2c_f32_f16_e32"
-        self.ones = "0x3f803f80" if bf16 else "0x3c003c00"
         self.out = []
         self.cold = []
         self.queue = []          # ids of LDS reads in flight, oldest first
@@ -143,161 +159,157 @@ class Gen:
         self.emit(f"s_waitcnt lgkmcnt({n_after})")
         self.queue = self.queue[i + 1:]
 
-    def k_read(self, unit, kb):
+    # fragment f of a unit's logits: key block f % MB, k-step f / MB
+    def k_text(self, unit, f, slot):
         st, c = (unit >> 1) % NSTAGE, unit & 1
-        off = st * KTILEB + c * 8 * KBLK + (kb >> 1) * 64
-        return self.lds_read(f"ds_read_b128 {KF(kb % 4)}, {KADDR(kb & 1)} offset:{off}")
+        off = st * KTILEB + (c * 8 + (f % MB) * 4) * KBLK + (f // MB) * 64
+        return f"ds_read_b128 {KF(slot)}, {KADDR} offset:{off}"
 
-    def v_read(self, unit, g):
+    def k_read(self, unit, f):
+        return self.lds_read(self.k_text(unit, f, f % 4))
+
+    def v_read_lo(self, unit, db):
         st, c = (unit >> 1) % NSTAGE, unit & 1
-        jj, db = g // DB, g % DB
-        off = st * TILEB + 4096 * (2 * c + jj)
-        self.lds_read(f"ds_read_b64_tr_b16 {VFlo(g % 4)}, {VADDR(db)} offset:{off}")
-        return self.lds_read(f"ds_read_b64_tr_b16 {VFhi(g % 4)}, {VADDR(db)} offset:{off + 2048}")
+        self.lds_read(f"ds_read_b64_tr_b16 {VFlo(db % 4)}, {VADDR(db)} offset:{st * TILEB + 8192 * c}")
+
+    def v_read_hi(self, unit, db):
+        st, c = (unit >> 1) % NSTAGE, unit & 1
+        return self.lds_read(f"ds_read_b64_tr_b16 {VFhi(db % 4)}, {VADDR(db)} offset:{st * TILEB + 8192 * c + 4096}")
+
+    def v_read(self, unit, db):
+        self.v_read_lo(unit, db)
+        return self.v_read_hi(unit, db)
+
+    def qk(self, b, qb, f, slot):
+        mb, kb = f % MB, f // MB
+        return f"{self.mfma} {X(b, qb, mb)}, {KF(slot)}, {Q(qb, kb)}, {'0' if kb == 0 else X(b, qb, mb)}"
+
+    def pv(self, b, qb, db):
+        if db == "ones":
+            return f"{self.mfma} {LSUM(qb)}, {ONES}, {P(b, qb)}, {LSUM(qb)}"
+        return f"{self.mfma} {O(qb, db)}, {VF(db % 4)}, {P(b, qb)}, {O(qb, db)}"
 
     # ---- the vector work of one unit and row block, as a list of instructions (buffer b)
-    def softmax_list(self, b, rb, interleave=True):
-        """In place: logits X[b][rb] -> exponentials against the current reference, packed as P[b][rb][0..1]; leaves
-        the unit's sums in temporaries: T0, T1 = partial sums of the exponentials (bf16; fp16: of the rounded ones),
-        and for bf16 T2, T3 = partial sums of the rounded ones.  The exponentials of one group of four elements
-        alternate with the additions / conversions of the previous group."""
+    def softmax_list(self, b, qb):
+        """In place: logits X[b][qb] -> exponentials against the current reference, packed as P[b][qb]; leaves in SUM the sum
+        of the exponentials (fp16: the largest).  The exponentials of the second group of four elements alternate with the
+        additions / conversions of the first."""
         L = []
-        ta, tb, tc, td = T(rb, 0), T(rb, 1), T(rb, 2), T(rb, 3)
-        if self.bf16:
-            L += [f"v_mov_b32 {tc}, 0", f"v_mov_b32 {td}, 0"]
-        else:
-            L += [f"v_mov_b32 {ta}, 0", f"v_mov_b32 {tb}, 0"]
+        acc = SUM(qb)
 
-        def consume_parts(g):          # elements 4g .. 4g+3: two pairs -> ([adds+cvt of pair 0], [.. pair 1], [dots])
-            parts, dots = [], []
-            for pr in (2 * g, 2 * g + 1):          # pair pr = elements 2pr, 2pr+1 -> register 8*jj + v2
-                jj, v2 = pr // 4, pr % 4
-                a, bb = x(b, rb, 2 * pr), x(b, rb, 2 * pr + 1)
-                dst = x(b, rb, 8 * jj + v2)
+        def consume_parts(g):          # elements 4g .. 4g+3: two pairs -> [adds+cvt of pair 0], [.. pair 1]
+            parts = []
+            for pr in (2 * g, 2 * g + 1):          # pair pr = elements 2pr, 2pr+1 -> register pr
+                a, bb = x(b, qb, 2 * pr), x(b, qb, 2 * pr + 1)
                 one = []
                 if self.bf16:
-                    acc = ta if pr % 2 == 0 else tb
-                    if pr < 2:
+                    if pr == 0:
                         one.append(f"v_add_f32 {acc}, {a}, {bb}")
                     else:
                         one.append(f"v_add_f32 {acc}, {acc}, {a}")
                         one.append(f"v_add_f32 {acc}, {acc}, {bb}")
-                one.append(f"{self.cvt} {dst}, {a}, {bb}")
+                elif pr == 0:
+                    one.append(f"v_max_f32 {acc}, {a}, {bb}")
+                else:
+                    one.append(f"v_max3_f32 {acc}, {acc}, {a}, {bb}")
+                one.append(f"{self.cvt} {x(b, qb, pr)}, {a}, {bb}")
                 parts.append(one)
-                acc = (tc if pr % 2 == 0 else td) if self.bf16 else (ta if pr % 2 == 0 else tb)
-                dots.append(f"{self.dot} {acc}, {self.ones}, {dst}")
-            return parts[0], parts[1], dots
+            return parts
 
-        for g in range(4):
+        for g in range(2):
             for i in range(4 * g, 4 * g + 4):
-                L.append(f"v_fma_f32 {x(b, rb, i)}, {x(b, rb, i)}, %[c], -{M_REF(rb)}")
-            ex = [f"v_exp_f32 {x(b, rb, i)}, {x(b, rb, i)}" for i in range(4 * g, 4 * g + 4)]
+                L.append(f"v_fma_f32 {x(b, qb, i)}, {x(b, qb, i)}, %[c], -{M_REF(qb)}")
+            ex = [f"v_exp_f32 {x(b, qb, i)}, {x(b, qb, i)}" for i in range(4 * g, 4 * g + 4)]
             if g == 0:
                 L += ex
             else:
-                p0, p1, dots = consume_parts(g - 1)
-                # the dot products read what the conversions wrote at least two instructions earlier
-                L += [ex[0]] + p0 + [ex[1]] + p1 + [ex[2], ex[3]] + dots
-        p0, p1, dots = consume_parts(3)
-        L += ["s_nop 1"] + p0 + p1 + ["s_nop 1"] + dots
-        return L
+                p0, p1 = consume_parts(0)
+                L += [ex[0]] + p0 + [ex[1]] + p1 + [ex[2], ex[3]]
+        p0, p1 = consume_parts(1)
+        return L + p0 + p1
 
-    def softmax_both(self, b):
-        """The two row blocks' lists, interleaved four instructions at a time (they share no register, so every
-        distance inside a list only grows)."""
-        A, B = self.softmax_list(b, 0), self.softmax_list(b, 1)
+    def softmax_all(self, b):
+        """The four row blocks' lists, interleaved an instruction at a time (they share no register)."""
+        S = [self.softmax_list(b, qb) for qb in range(QB)]
         L = []
-        for i in range(0, max(len(A), len(B)), 4):
-            L += A[i:i + 4]
-            L += B[i:i + 4]
+        for i in range(len(S[0])):
+            for q in range(QB):
+                L.append(S[q][i])
         return L
 
     def pending_sums(self):
-        """Adds the previous unit's sums (left in the temporaries by its vector work and its check) to the running
-        sums: the first vector instructions of the next step, or of the drain."""
-        L = []
-        for rb in (0, 1):
-            ta, tb, tc, td = T(rb, 0), T(rb, 1), T(rb, 2), T(rb, 3)
-            L.append(f"v_add_f32 {L_RUN(rb)}, {L_RUN(rb)}, {ta}")
-            if self.bf16:
-                L.append(f"v_add_f32 {tc}, {tc}, {td}")
-        if self.bf16:
-            for rb in (0, 1):
-                L.append(f"v_add_f32 {L_RND(rb)}, {L_RND(rb)}, {T(rb, 2)}")
-        return L
+        """Adds the previous unit's sums (left in the temporaries by its vector work) to the running sums: the first
+        vector instructions of the next step, or of the drain."""
+        return [f"v_add_f32 {L_RUN(qb)}, {L_RUN(qb)}, {SUM(qb)}" for qb in range(QB)] if self.bf16 else []
 
     def check_list(self):
-        """Both row blocks' sums and the test sum <= 256 (which proves that no exponential exceeded 256), leaving the
-        outcome in vcc: the last vector instructions of a step."""
-        L = ["s_nop 3"]
-        for rb in (0, 1):
-            L.append(f"v_add_f32 {T(rb, 0)}, {T(rb, 0)}, {T(rb, 1)}")
-        L.append(f"v_cmp_nge_f32 vcc, 0x43800000, {T(0, 0)}")        # not (256 >= sum): also true for inf and NaN
-        L.append("s_mov_b64 s[68:69], vcc")
-        L.append(f"v_cmp_nge_f32 vcc, 0x43800000, {T(1, 0)}")
-        L.append("s_or_b64 vcc, vcc, s[68:69]")
+        """The test "the sum over all row blocks <= 256" (fp16: the largest), which proves that no exponential exceeded 256,
+        leaving the outcome in vcc: the last vector instructions of a step."""
+        if self.bf16:
+            L = [f"v_add_f32 {T4}, {SUM(0)}, {SUM(1)}", f"v_add_f32 {T5}, {SUM(2)}, {SUM(3)}", f"v_add_f32 {T4}, {T4}, {T5}"]
+        else:
+            L = [f"v_max_f32 {T4}, {SUM(0)}, {SUM(1)}", f"v_max3_f32 {T4}, {T4}, {SUM(2)}, {SUM(3)}"]
+        L.append(f"v_cmp_nge_f32 vcc, 0x43800000, {T4}")             # not (256 >= sum): also true for inf and NaN
         return L
 
     def finish_sums(self, unit, inflight_text):
-        """After the step's last matrix instruction: if some sum exceeded 256, a block out of line computes both row
-        blocks' logits again, moves the references up to the row maxima, rescales, and redoes the exponentials."""
+        """After the step's last matrix instruction: if the sum exceeded 256, a block out of line computes the row blocks'
+        logits again, moves the references up to the row maxima, rescales, and redoes the exponentials."""
         e = self.emit
         b = unit % 4
         k = self.nlabel
         self.nlabel += 1
+        e("s_and_b64 vcc, vcc, exec")
         e(f"s_cbranch_vccnz .Lfw64_redo_{k}_%=")
         e(f".Lfw64_back_{k}_%=:")
         # ---- the block out of line
         main, self.out = self.out, []
-        st, c = (unit >> 1) % NSTAGE, unit & 1
         e(f".Lfw64_redo_{k}_%=:")
         e("s_waitcnt lgkmcnt(0)")
-        for rb in (0, 1):
-            ta, tb = T(rb, 0), T(rb, 1)
-            t4, t5 = T(rb, 4), T(rb, 5)
-            for kb in range(KB):
-                off = st * KTILEB + c * 8 * KBLK + (kb >> 1) * 64
-                e(f"ds_read_b128 {KF(3)}, {KADDR(kb & 1)} offset:{off}")
-                e("s_waitcnt lgkmcnt(0)")
-                e(f"{self.mfma} {X(b, rb)}, {KF(3)}, {Q(rb, kb)}, {'0' if kb == 0 else X(b, rb)}")
-            e("s_nop 15")
-            e("s_nop 3")
-            e(f"v_max3_f32 {t4}, {x(b, rb, 0)}, {x(b, rb, 1)}, {x(b, rb, 2)}")
-            for i in range(3, 15, 2):
-                e(f"v_max3_f32 {t4}, {t4}, {x(b, rb, i)}, {x(b, rb, i + 1)}")
-            e(f"v_max_f32 {t4}, {t4}, {x(b, rb, 15)}")
-            e(f"v_mov_b32 {t5}, {t4}")
+        for f in range(MB * KB):
+            e(self.k_text(unit, f, 3))
+            e("s_waitcnt lgkmcnt(0)")
+            for qb in range(QB):
+                e(self.qk(b, qb, f, 3))
+            e("s_nop 7")
+        e("s_nop 15")
+        e("s_nop 3")
+        for qb in range(QB):
+            e(f"v_max3_f32 {T4}, {x(b, qb, 0)}, {x(b, qb, 1)}, {x(b, qb, 2)}")
+            for i in (3, 5):
+                e(f"v_max3_f32 {T4}, {T4}, {x(b, qb, i)}, {x(b, qb, i + 1)}")
+            e(f"v_max_f32 {T4}, {T4}, {x(b, qb, 7)}")
+            for swap in ("v_permlane32_swap_b32_e32", "v_permlane16_swap_b32_e32"):   # the lane groups hold different keys of one query
+                e(f"v_mov_b32 {T5}, {T4}")
+                e("s_nop 1")
+                e(f"{swap} {T4}, {T5}")
+                e("s_nop 1")
+                e(f"v_max_f32 {T4}, {T4}, {T5}")
+            e(f"v_mul_f32 {T4}, %[c], {T4}")                # in log2 units
+            e(f"v_cmp_gt_f32 vcc, {T4}, {M_REF(qb)}")
+            e(f"v_sub_f32 {T5}, {M_REF(qb)}, {T4}")
+            e(f"v_exp_f32 {T5}, {T5}")
+            e(f"v_cndmask_b32 {M_REF(qb)}, {M_REF(qb)}, {T4}, vcc")
             e("s_nop 1")
-            e(f"v_permlane32_swap_b32_e32 {t4}, {t5}")      # the two half-waves hold different keys of one query
-            e("s_nop 1")
-            e(f"v_max_f32 {t4}, {t4}, {t5}")
-            e(f"v_mul_f32 {t4}, %[c], {t4}")                # in log2 units
-            e(f"v_cmp_gt_f32 vcc, {t4}, {M_REF(rb)}")
-            e(f"v_sub_f32 {t5}, {M_REF(rb)}, {t4}")
-            e(f"v_exp_f32 {t5}, {t5}")
-            e(f"v_cndmask_b32 {M_REF(rb)}, {M_REF(rb)}, {t4}, vcc")
-            e("s_nop 1")
-            e(f"v_cndmask_b32 {t5}, 1.0, {t5}, vcc")
-            e(f"v_mul_f32 {L_RUN(rb)}, {t5}, {L_RUN(rb)}")
+            e(f"v_cndmask_b32 {T5}, 1.0, {T5}, vcc")
             if self.bf16:
-                e(f"v_mul_f32 {L_RND(rb)}, {t5}, {L_RND(rb)}")
+                e(f"v_mul_f32 {L_RUN(qb)}, {T5}, {L_RUN(qb)}")
             # the accumulators live in AGPRs: out, times alpha, back in -- four at a time through the K fragment
             # registers of slot 3 (free here); the second products issued earlier in this step have long retired
             # (the 20 wait states above), and the matrix instructions that follow read them as their C operand
             tmp = [f"v{128 + 12 + i}" for i in range(4)]
-            for i0 in range(0, 64, 4):
+            for r0 in [4 * DB * qb + 4 * db for db in range(DB)] + [192 + 4 * qb]:
                 for i in range(4):
-                    e(f"v_accvgpr_read_b32 {tmp[i]}, a{64 * rb + i0 + i}")
+                    e(f"v_accvgpr_read_b32 {tmp[i]}, a{r0 + i}")
                 e("s_nop 0")
                 for i in range(4):
-                    e(f"v_mul_f32 {tmp[i]}, {t5}, {tmp[i]}")
+                    e(f"v_mul_f32 {tmp[i]}, {T5}, {tmp[i]}")
                 e("s_nop 0")
                 for i in range(4):
-                    e(f"v_accvgpr_write_b32 a{64 * rb + i0 + i}, {tmp[i]}")
-            for ln in self.softmax_list(b, rb):
+                    e(f"v_accvgpr_write_b32 a{r0 + i}, {tmp[i]}")
+            for ln in self.softmax_list(b, qb):
                 e(ln)
-            e("s_nop 3")
-            e(f"v_add_f32 {ta}, {ta}, {tb}")
+                e("s_nop 0")       # (a result of v_exp is read two or more instructions later)
         for ln in inflight_text:
             e(ln)
         e("s_nop 7")
@@ -305,103 +317,104 @@ class Gen:
         self.cold += self.out
         self.out = main
 
-    def dma_groups(self, tile):
-        """This wave's share of the loads of a tile as a list of short groups of instructions (one load each, then
-        the advance of the two tile pointers s[60:61] / s[62:63]), to be spread over a step."""
+    def dma_list(self, tile):
+        """This wave's share of the loads of a tile, then the advance of the two tile pointers s[60:61] / s[62:63], to be
+        spread over a step.  (Between m0's new value and the load that reads it something else has to issue.)"""
         st = tile % NSTAGE
         G = []
         for tensor in (0, 1):
             ptr = "s[60:61]" if tensor == 0 else "s[62:63]"
             for n in range(NI):
                 if tensor == 0:
-                    g = [f"s_add_u32 m0, %[ldsk], {st * KTILEB + NW * n * KBLK}"]
+                    G.append(f"s_add_u32 m0, %[ldsk], {st * KTILEB + NW * n * KBLK}")
                 else:
-                    g = [f"s_add_u32 m0, %[ldsv], {st * TILEB + NW * n * 1024}"]
-                g.append("s_nop 0")
-                g.append(f"global_load_lds_dwordx4 {DMAOFF(tensor, n)}, {ptr} offset:0")
-                G.append(g)
-        G.append([f"s_add_u32 s60, s60, {TILEB}", "s_addc_u32 s61, s61, 0",
-                  f"s_add_u32 s62, s62, {TILEB}", "s_addc_u32 s63, s63, 0"])
+                    G.append(f"s_add_u32 m0, %[ldsv], {st * TILEB + NW * n * 1024}")
+                G.append(f"global_load_lds_dwordx4 {DMAOFF(tensor, n)}, {ptr} offset:0")
+        G += [f"s_add_u32 s60, s60, {TILEB}", "s_addc_u32 s61, s61, 0", f"s_add_u32 s62, s62, {TILEB}", "s_addc_u32 s63, s63, 0"]
         return G
+
+    @staticmethod
+    def check_distances(lines):
+        """In a stream of vector instructions (whatever is issued in between only widens the distances) a result of v_exp is
+        read two or more instructions later, which the hardware does not watch."""
+        exp_at = {}
+        for pos, ln in enumerate(lines):
+            op, _, rest = ln.partition(" ")
+            regs = [r.strip().lstrip("-") for r in rest.split(",")]
+            for r in regs[1:]:
+                assert pos - exp_at.get(r, -2) >= 2, ln
+            exp_at.pop(regs[0], None)
+            if op == "v_exp_f32":
+                exp_at[regs[0]] = pos
 
     @staticmethod
     def cost(ln):
         op = ln.split()[0]
         if op == "v_exp_f32":
             return 8
-        if op == "s_nop":
-            return int(ln.split()[1]) + 1
-        if op.startswith("s_"):
-            return 2
         return 4
 
     # ---- one step: logits of unit u+1, softmax of unit u, second product of unit u-1.
-    # kpre: read ids of K fragments 0..2 of unit u+1, already issued.  dma: groups of load instructions to spread
-    # over the step (the loads requested behind the barrier that ended the previous step).
+    # kpre: read ids of K fragments 0..2 of unit u+1, already issued.  dma: load instructions to spread over the step (the
+    # loads requested behind the barrier that ended the previous step).
     def step(self, u, kpre, with_pv=True, dma=()):
         e = self.emit
-        valu = (self.pending_sums() if u > 0 else []) + self.softmax_both(u % 4) + self.check_list()
-        # the load groups go in between, evenly
-        groups = [[ln] for ln in valu]
-        if dma:
-            every = max(1, len(groups) // (len(dma) + 1))
-            for gi, g in enumerate(dma):
-                groups.insert(min(len(groups), (gi + 1) * every + gi), list(g))
+        valu = (self.pending_sums() if u > 0 else []) + self.softmax_all(u % 4) + self.check_list()
+        self.check_distances(valu)
+        dma = list(dma)
         xq, xp = (u + 1) % 4, (u - 1) % 4
+        nf = MB * KB                             # fragments of a unit's logits; as many of its second product
+        assert nf == DB
         if with_pv:
-            slots = [("qk", 0), ("qk", 1), ("qk", 2)]
-            for i in range(3, 8):
+            slots = [("qk", 0), ("pv", "ones"), ("qk", 1), ("qk", 2)]
+            for i in range(3, nf):
                 slots += [("qk", i), ("pv", i - 3)]
-            slots += [("pv", 5), ("pv", 6), ("pv", 7)]
+            slots += [("pv", i) for i in range(nf - 3, nf)]
         else:
-            slots = [("qk", i) for i in range(8)]
-        nsub = 2 * len(slots)                    # two matrix instructions per slot
-        total = sum(self.cost(ln) for g in groups for ln in g)
+            slots = [("qk", i) for i in range(nf)]
+        nsub = QB * len(slots)                   # a slot's matrix instructions share its fragment
+        total = sum(self.cost(ln) for ln in valu)
         kids = dict(enumerate(kpre))
         vids = {}
         next_k = None
         inflight_next = []        # text of the next step's K prefetch, for the block out of line
         sub = 0
         done_cost = 0
-        gi = 0
+        vi = 0
         for si, (kind, i) in enumerate(slots):
-            for rb in (0, 1):
-                n_before = len(self.out)
+            for n in range(QB):
+                qb = QB - 1 - n if si & 1 else n
+                if n == 0 and i != "ones":
+                    self.wait_for(kids[i] if kind == "qk" else vids[i])
                 if kind == "qk":
-                    if rb == 0:
-                        self.wait_for(kids[i])
-                        n_before = len(self.out)
-                    e(f"{self.mfma} {X(xq, rb)}, {KF(i % 4)}, {Q(rb, i)}, {'0' if i == 0 else X(xq, rb)}")
-                    if rb == 1:
-                        if i + 3 < KB:
-                            kids[i + 3] = self.k_read(u + 1, i + 3)
-                        if with_pv and i < 3:
-                            vids[i] = self.v_read(u - 1, i)
+                    e(self.qk(xq, qb, i, i % 4))
                 else:
-                    if rb == 0:
-                        self.wait_for(vids[i])
-                        n_before = len(self.out)
-                    jj, db = i // DB, i % DB
-                    e(f"{self.mfma} {O(rb, db)}, {VF(i % 4)}, {P(xp, rb, jj)}, {O(rb, db)}")
-                    if rb == 1 and i + 3 < 2 * DB:
-                        vids[i + 3] = self.v_read(u - 1, i + 3)
+                    e(self.pv(xp, qb, i))
+                # one LDS read or load instruction
+                if kind == "qk" and n == 1 and i + 3 < nf:
+                    kids[i + 3] = self.k_read(u + 1, i + 3)
+                elif kind == "qk" and with_pv and i < 3 and n == 2:
+                    self.v_read_lo(u - 1, i)
+                elif kind == "qk" and with_pv and i < 3 and n == 3:
+                    vids[i] = self.v_read_hi(u - 1, i)
+                elif kind == "pv" and i != "ones" and i + 3 < nf and n == 1:
+                    self.v_read_lo(u - 1, i + 3)
+                elif kind == "pv" and i != "ones" and i + 3 < nf and n == 2:
+                    vids[i + 3] = self.v_read_hi(u - 1, i + 3)
+                elif dma:
+                    e(dma.pop(0))
                 sub += 1
-                # vector (and load) instructions behind this matrix instruction: as many as issue while it runs
-                # (CAP cycles, less what the LDS reads just issued take), never fewer than an even share
-                n_lds = len(self.out) - n_before - 1
-                room = CAP - 4 * n_lds
                 used = 0
                 goal = total * sub / nsub
-                while gi < len(groups):
-                    c = sum(self.cost(l) for l in groups[gi])
-                    if sub < nsub and used + c > room and done_cost + c / 2 > goal:
+                while vi < len(valu):
+                    c = self.cost(valu[vi])
+                    if sub < nsub and used + c > CAP and done_cost + c / 2 > goal:
                         break
-                    for ln in groups[gi]:
-                        e(ln)
+                    e(valu[vi])
                     done_cost += c
                     used += c
-                    gi += 1
-        assert gi == len(groups)
+                    vi += 1
+        assert vi == len(valu) and not dma
         odd = u & 1
         if odd:
             # the next step's logits read the same tile: its first fragments go out now
@@ -415,7 +428,7 @@ class Gen:
             # newest tile's), tile u/2-1 is free; this wave's share of tile u/2+3 goes out during the next step
             e(f"s_waitcnt vmcnt({2 * NI})")
             e("s_barrier")
-            next_dma = self.dma_groups(u // 2 + 3)
+            next_dma = self.dma_list(u // 2 + 3)
             next_k = [self.k_read(u + 2, f) for f in range(3)]
         return next_k, next_dma
 
@@ -425,13 +438,14 @@ class Gen:
         self.emit("s_waitcnt lgkmcnt(0)")      # the K fragments read ahead for a step that does not come
         self.queue = []
         vids = {g: self.v_read(u, g) for g in range(3)}
-        for g in range(2 * DB):
+        for g in range(DB):
             self.wait_for(vids[g])
-            jj, db = g // DB, g % DB
-            for rb in (0, 1):
-                e(f"{self.mfma} {O(rb, db)}, {VF(g % 4)}, {P(u % 4, rb, jj)}, {O(rb, db)}")
-            if g + 3 < 2 * DB:
+            for qb in range(QB):
+                e(self.pv(u % 4, qb, g))
+            if g + 3 < DB:
                 vids[g + 3] = self.v_read(u, g + 3)
+        for qb in range(QB):
+            e(self.pv(u % 4, qb, "ones"))
         assert not self.queue
         for ln in self.pending_sums():
             e(ln)
@@ -439,34 +453,33 @@ class Gen:
 
     def block(self):
         e = self.emit
-        e(f"v_xor_b32 {KADDR(1)}, 32, {KADDR(0)}")
-        e(f"v_xor_b32 {VADDR(1)}, 64, {VADDR(0)}")
-        e(f"v_xor_b32 {VADDR(2)}, 128, {VADDR(0)}")
-        e(f"v_xor_b32 {VADDR(3)}, 192, {VADDR(0)}")
+        for db in range(1, DB):
+            e(f"v_xor_b32 {VADDR(db)}, {32 * db}, {VADDR(0)}")
         for tensor in (0, 1):
             for n in range(NI):
                 e(f"v_add_u32 {DMAOFF(tensor, n)}, {n * NW * 1024}, {KVOFF if tensor == 0 else VVOFF}")
         e("s_mov_b64 s[60:61], %[kptr]")
         e("s_mov_b64 s[62:63], %[vptr]")
         e("s_mov_b32 s67, %[npairs]")
-        for r in range(128):
+        for r in list(range(128)) + list(range(192, 208)):
             e(f"v_accvgpr_write_b32 a{r}, 0")
-        for rb in (0, 1):
-            e(f"v_mov_b32 {M_REF(rb)}, 0xf149f2ca")    # -1e30
-            e(f"v_mov_b32 {L_RUN(rb)}, 0")
-            e(f"v_mov_b32 {L_RND(rb)}, 0")
+        for r in range(168, 172):
+            e(f"v_mov_b32 v{r}, {'0x3f803f80' if self.bf16 else '0x3c003c00'}")
+        for qb in range(QB):
+            e(f"v_mov_b32 {M_REF(qb)}, 0xf149f2ca")    # -1e30
+            e(f"v_mov_b32 {L_RUN(qb)}, 0")
         # this wave's share of tile 2 (tiles 0 and 1 were issued, tile 0 published, before the block)
-        for g in self.dma_groups(2):
-            for ln in g:
-                e(ln)
+        for ln in self.dma_list(2):
+            e(ln)
+            e("s_nop 0")
         # logits of unit 0
         ids = [self.k_read(0, f) for f in range(3)]
-        for kb in range(KB):
-            self.wait_for(ids[kb])
-            for rb in (0, 1):
-                e(f"{self.mfma} {X(0, rb)}, {KF(kb % 4)}, {Q(rb, kb)}, {'0' if kb == 0 else X(0, rb)}")
-            if kb + 3 < KB:
-                ids.append(self.k_read(0, kb + 3))
+        for f in range(MB * KB):
+            self.wait_for(ids[f])
+            for qb in range(QB):
+                e(self.qk(0, qb, f, f % 4))
+            if f + 3 < MB * KB:
+                ids.append(self.k_read(0, f + 3))
         kpre = [self.k_read(1, f) for f in range(3)]
         e("s_nop 15")                               # the first step's vector work reads these logits
         kpre, dma = self.step(0, kpre, with_pv=False)
@@ -500,8 +513,8 @@ class Gen:
         return "\n".join(self.out)
 
 
-CLOBBER_V = list(range(0, 160)) + [167, 169, 170, 171] + list(range(174, 194))
-CLOBBER_S = list(range(60, 70))
+CLOBBER_V = list(range(0, 160)) + list(range(168, 172)) + list(range(174, 181)) + list(range(183, 201))
+CLOBBER_S = list(range(60, 68))
 
 
 def generate(path):

@@ -14,7 +14,7 @@ SRC = os.path.join(HERE, "csrc", "fa_fwd.hip")
 HDR = os.path.join(os.path.dirname(HERE), "include", "fa.h")
 # fragments of the one translation unit, included by fa_fwd.hip
 FRAGMENTS = [os.path.join(HERE, "csrc", n) for n in (
-    "fa_types.inc", "fa_mask.inc", "fa_device.inc", "fa_attention_kernel.inc", "fa_attention_wide64_kernel.inc",
+    "fa_types.inc", "fa_mask.inc", "fa_device.inc", "fa_row_tile.inc", "fa_attention_kernel.inc", "fa_attention_wide64_kernel.inc",
     "fa_attention_rows_kernel.inc",
     "fa_linear_kernel.inc", "fa_decode_kernels.inc", "gen_fa_wide64_loop.py")]
 # written by gen_fa_wide64_loop.py at build time (hand-scheduled assembly of a regular loop: generated, not typed)

@@ -8,6 +8,7 @@
 // others get a per-element predicate computed from indices -- no mask tensor exists.
 //
 // Where things are (the .inc files are fragments of this one translation unit, included below):
+//  * fa_row_tile.inc -- one wave's rows and the work of one tile on them, for fa_fwd_kernel.
 //  * fa_attention_kernel.inc -- fa_fwd_kernel, the attention kernel, one source for most variants (template
 //    flags): WIDE (all NW waves walk the same tiles: 256 query rows with eight, 128 with four) or split (128 rows,
 //    two groups of four waves on alternate tiles, merged through LDS); CAUSAL; PAIR (folded rows for short causal
@@ -29,13 +30,14 @@
 // gfx950 mapping common to all variants of the attention kernel (this library's own design):
 //  * one wavefront owns 32 query rows; a SIMD holds two wavefronts, of one workgroup of eight or of two
 //    workgroups of four.  Each wavefront runs a tile as three clusters (logits, softmax, second
-//    product); overlap of the matrix and vector units comes mostly from the two wavefronts of a SIMD
-//    being in different clusters; those of a workgroup run free between its one barrier per tile.
-//  * logits are produced TRANSPOSED, S^T = K Q^T, with v_mfma_f32_32x32x16: keys on the
-//    M side (A operand, read from LDS with ds_read_b128), queries on the N side (B
-//    operand, held in registers for the whole kernel).  A lane then owns ONE query
-//    column, so row max / row sum are in-lane reductions plus a single cross-half
-//    exchange (v_permlane32_swap), and the exponentiated tile is already in the
+//    product), or with the softmax dealt out among the products (fa_row_tile.inc).  In clusters the overlap of the matrix
+//    and vector units comes mostly from the two wavefronts of a SIMD being in different ones; those of a workgroup run
+//    free between its one barrier per tile.
+//  * logits are produced TRANSPOSED, S^T = K Q^T, with v_mfma_f32_16x16x32 (v_mfma_f32_32x32x16 where few workgroups are
+//    bound by their chain of tiles): keys on the M side (A operand, read from LDS with ds_read_b128), queries on the N
+//    side (B operand, held in registers for the whole kernel).  A lane then owns one query column or two, so row
+//    max / row sum are in-lane reductions plus exchanges between four lanes or two (v_permlane32_swap,
+//    v_permlane16_swap), and the exponentiated tile is already in the
 //    B-operand register layout of the second product O^T = V^T P^T (no shuffle, no LDS
 //    round trip -- the MFMA counterpart of the paper's appendix-B layout converter).
 //  * V^T fragments come straight out of the row-major V tile with the transposing LDS
@@ -68,6 +70,7 @@ namespace {
 #include "fa_types.inc"
 #include "fa_mask.inc"
 #include "fa_device.inc"
+#include "fa_row_tile.inc"
 #include "fa_attention_kernel.inc"
 #include "fa_attention_wide64_kernel.inc"
 #include "fa_attention_rows_kernel.inc"

@@ -50,6 +50,12 @@ LDS: four stages of (K tile, V tile); tile t lives in stage t % 4.  Barrier k (t
 as in the compiler-scheduled loop around this block) publishes tile k+1 and certifies that no wave reads tile k-1
 any more; between barrier k and barrier k+1 every wave issues its share (four loads per tensor) of tile k+3.
 
+The reads ahead do not stop between steps: a step ends with reads of the next one's first fragments and begins with second
+products, whose V^T fragments need no barrier, while the first K fragments of a tile just published are on their way.  The
+barrier stands in an even step behind its last wait for V.  (Barrier and first K fragments between the steps, with the
+logits first, left the matrix pipe idle for the LDS latency once a tile: 1 x 32 x 131072 103.4 ms, now 101.6; 8 x 32 x
+8192 3776 us, 3742, fp16 3947, 3813; 512 queries on 32768 keys 250.5, 246.2.)
+
 Steps: the block computes S(0), runs step 0 (no second product yet), then the steady loop -- eight steps per pass,
 so that buffers and stages come round to where they started -- and leaves after step 2J-1 (J = number of tiles, even)
 through one of two exits, each followed by the second product of the last unit.
@@ -138,15 +144,17 @@ class Gen:
         self.cold = []
         self.queue = []          # ids of LDS reads in flight, oldest first
         self.next_id = 0
+        self.labels = {}
         self.nlabel = 0
 
     def emit(self, line):
         self.out.append(line)
 
     # ---- LDS reads and the waits for them (reads return in order)
-    def lds_read(self, text):
+    def lds_read(self, text, label):
         self.emit(text)
         self.queue.append(self.next_id)
+        self.labels[self.next_id] = label
         self.next_id += 1
         return self.next_id - 1
 
@@ -166,15 +174,15 @@ class Gen:
         return f"ds_read_b128 {KF(slot)}, {KADDR} offset:{off}"
 
     def k_read(self, unit, f):
-        return self.lds_read(self.k_text(unit, f, f % 4))
+        return self.lds_read(self.k_text(unit, f, f % 4), ("k", f))
 
     def v_read_lo(self, unit, db):
         st, c = (unit >> 1) % NSTAGE, unit & 1
-        self.lds_read(f"ds_read_b64_tr_b16 {VFlo(db % 4)}, {VADDR(db)} offset:{st * TILEB + 8192 * c}")
+        self.lds_read(f"ds_read_b64_tr_b16 {VFlo(db % 4)}, {VADDR(db)} offset:{st * TILEB + 8192 * c}", ("vlo", db))
 
     def v_read_hi(self, unit, db):
         st, c = (unit >> 1) % NSTAGE, unit & 1
-        return self.lds_read(f"ds_read_b64_tr_b16 {VFhi(db % 4)}, {VADDR(db)} offset:{st * TILEB + 8192 * c + 4096}")
+        return self.lds_read(f"ds_read_b64_tr_b16 {VFhi(db % 4)}, {VADDR(db)} offset:{st * TILEB + 8192 * c + 4096}", ("vhi", db))
 
     def v_read(self, unit, db):
         self.v_read_lo(unit, db)
@@ -252,7 +260,7 @@ class Gen:
         L.append(f"v_cmp_nge_f32 vcc, 0x43800000, {T4}")             # not (256 >= sum): also true for inf and NaN
         return L
 
-    def finish_sums(self, unit, inflight_text):
+    def finish_sums(self, unit):
         """After the step's last matrix instruction: if the sum exceeded 256, a block out of line computes the row blocks'
         logits again, moves the references up to the row maxima, rescales, and redoes the exponentials."""
         e = self.emit
@@ -267,7 +275,7 @@ class Gen:
         e(f".Lfw64_redo_{k}_%=:")
         e("s_waitcnt lgkmcnt(0)")
         for f in range(MB * KB):
-            e(self.k_text(unit, f, 3))
+            e(self.k_text(unit, f, 3))               # (slot 3 is free between steps)
             e("s_waitcnt lgkmcnt(0)")
             for qb in range(QB):
                 e(self.qk(b, qb, f, 3))
@@ -310,9 +318,7 @@ class Gen:
             for ln in self.softmax_list(b, qb):
                 e(ln)
                 e("s_nop 0")       # (a result of v_exp is read two or more instructions later)
-        for ln in inflight_text:
-            e(ln)
-        e("s_nop 7")
+        e("s_nop 7")               # (the fragments read ahead have landed: the main path's waits find fewer reads in flight)
         e(f"s_branch .Lfw64_back_{k}_%=")
         self.cold += self.out
         self.out = main
@@ -355,32 +361,44 @@ class Gen:
         return 4
 
     # ---- one step: logits of unit u+1, softmax of unit u, second product of unit u-1.
-    # kpre: read ids of K fragments 0..2 of unit u+1, already issued.  dma: load instructions to spread over the step (the
-    # loads requested behind the barrier that ended the previous step).
-    def step(self, u, kpre, with_pv=True, dma=()):
+    # kpre, vpre: read ids of K fragments 0..2 of unit u+1 and V^T fragments 0..2 of unit u-1, already issued.  dma: load
+    # instructions to spread over the step (those of the tile whose stage the barrier of the previous step set free).
+    # Fragments are read three ahead without a gap between steps.  Even steps hold the barrier of tile u/2: it comes when the
+    # last fragment of V of unit u-1 has arrived (nobody reads tile u/2-1 any more) and with the first fragments of tile u/2+1
+    # to be read behind it, which are needed after a dozen other matrix instructions.
+    def step(self, u, kpre, vpre, dma=()):
         e = self.emit
+        with_pv = u > 0
         valu = (self.pending_sums() if u > 0 else []) + self.softmax_all(u % 4) + self.check_list()
         self.check_distances(valu)
         dma = list(dma)
         xq, xp = (u + 1) % 4, (u - 1) % 4
         nf = MB * KB                             # fragments of a unit's logits; as many of its second product
-        assert nf == DB
+        assert nf == DB == 8
         if with_pv:
-            slots = [("qk", 0), ("pv", "ones"), ("qk", 1), ("qk", 2)]
-            for i in range(3, nf):
-                slots += [("qk", i), ("pv", i - 3)]
-            slots += [("pv", i) for i in range(nf - 3, nf)]
+            slots = [("pv", "ones"), ("pv", 0), ("pv", 1), ("qk", 0), ("qk", 1)]
+            for i in range(2, 6):
+                slots += [("pv", i), ("qk", i)]
+            slots += [("pv", 6), ("qk", 6), ("qk", 7), ("pv", 7)]
         else:
             slots = [("qk", i) for i in range(nf)]
         nsub = QB * len(slots)                   # a slot's matrix instructions share its fragment
         total = sum(self.cost(ln) for ln in valu)
         kids = dict(enumerate(kpre))
-        vids = {}
-        next_k = None
-        inflight_next = []        # text of the next step's K prefetch, for the block out of line
+        vids = dict(enumerate(vpre))
+        next_k, next_v = [], []
         sub = 0
         done_cost = 0
         vi = 0
+
+        def publish():
+            """Even steps: tile u/2+1 is published (this wave's share has landed: all loads but the newest tile's)."""
+            if u & 1 == 0:
+                if with_pv:
+                    self.wait_for(vids[nf - 1])
+                e(f"s_waitcnt vmcnt({2 * NI})")
+                e("s_barrier")
+
         for si, (kind, i) in enumerate(slots):
             for n in range(QB):
                 qb = QB - 1 - n if si & 1 else n
@@ -391,17 +409,30 @@ class Gen:
                 else:
                     e(self.pv(xp, qb, i))
                 # one LDS read or load instruction
-                if kind == "qk" and n == 1 and i + 3 < nf:
-                    kids[i + 3] = self.k_read(u + 1, i + 3)
-                elif kind == "qk" and with_pv and i < 3 and n == 2:
-                    self.v_read_lo(u - 1, i)
-                elif kind == "qk" and with_pv and i < 3 and n == 3:
-                    vids[i] = self.v_read_hi(u - 1, i)
-                elif kind == "pv" and i != "ones" and i + 3 < nf and n == 1:
-                    self.v_read_lo(u - 1, i + 3)
-                elif kind == "pv" and i != "ones" and i + 3 < nf and n == 2:
-                    vids[i + 3] = self.v_read_hi(u - 1, i + 3)
-                elif dma:
+                if kind == "qk" and i + 3 < nf:
+                    if n == 1:
+                        kids[i + 3] = self.k_read(u + 1, i + 3)
+                        free = False
+                    else:
+                        free = True
+                elif kind == "qk" and with_pv and (i, n) in ((6, 1), (6, 2), (7, 1)):
+                    next_k.append(self.k_read(u + 2, len(next_k)))
+                    free = False
+                elif kind == "pv" and i != "ones" and n in (1, 2):
+                    f = i + 3
+                    unit, db = (u - 1, f) if f < nf else (u, f - nf)
+                    if n == 1:
+                        self.v_read_lo(unit, db)
+                    else:
+                        rid = self.v_read_hi(unit, db)
+                        if f < nf:
+                            vids[f] = rid
+                        else:
+                            next_v.append(rid)
+                    free = False
+                else:
+                    free = True
+                if free and dma:
                     e(dma.pop(0))
                 sub += 1
                 used = 0
@@ -414,30 +445,24 @@ class Gen:
                     done_cost += c
                     used += c
                     vi += 1
+            if kind == "pv" and i == 6:
+                publish()
         assert vi == len(valu) and not dma
-        odd = u & 1
-        if odd:
-            # the next step's logits read the same tile: its first fragments go out now
-            n0 = len(self.out)
+        if not with_pv:
+            # the reads ahead, in the order of the other steps
+            next_v = [self.v_read(u, 0), self.v_read(u, 1)]
+            publish()
             next_k = [self.k_read(u + 2, f) for f in range(3)]
-            inflight_next = self.out[n0:]
-        self.finish_sums(u, inflight_next)
-        next_dma = []
-        if not odd:
-            # mid-tile barrier number u/2: tile u/2+1 is published (this wave's share has landed: all loads but the
-            # newest tile's), tile u/2-1 is free; this wave's share of tile u/2+3 goes out during the next step
-            e(f"s_waitcnt vmcnt({2 * NI})")
-            e("s_barrier")
-            next_dma = self.dma_list(u // 2 + 3)
-            next_k = [self.k_read(u + 2, f) for f in range(3)]
-        return next_k, next_dma
+            next_v.append(self.v_read(u, 2))
+        self.finish_sums(u)
+        # this wave's share of tile u/2+3 goes out during the step after the barrier
+        next_dma = self.dma_list(u // 2 + 3) if u & 1 == 0 else []
+        return next_k, next_v, next_dma
 
-    def drain(self, u):
+    def drain(self, u, vpre):
         """Second product of unit u after the last step, and that unit's sums."""
         e = self.emit
-        self.emit("s_waitcnt lgkmcnt(0)")      # the K fragments read ahead for a step that does not come
-        self.queue = []
-        vids = {g: self.v_read(u, g) for g in range(3)}
+        vids = dict(enumerate(vpre))
         for g in range(DB):
             self.wait_for(vids[g])
             for qb in range(QB):
@@ -446,9 +471,10 @@ class Gen:
                 vids[g + 3] = self.v_read(u, g + 3)
         for qb in range(QB):
             e(self.pv(u % 4, qb, "ones"))
-        assert not self.queue
         for ln in self.pending_sums():
             e(ln)
+        self.emit("s_waitcnt lgkmcnt(0)")      # the K fragments read ahead for a step that does not come
+        self.queue = []
         e("s_branch .Lfw64_end_%=")
 
     def block(self):
@@ -482,30 +508,30 @@ class Gen:
                 ids.append(self.k_read(0, f + 3))
         kpre = [self.k_read(1, f) for f in range(3)]
         e("s_nop 15")                               # the first step's vector work reads these logits
-        kpre, dma = self.step(0, kpre, with_pv=False)
+        kpre, vpre, dma = self.step(0, kpre, [])
         e(".Lfw64_loop_%=:")
-        entry_queue = list(self.queue)
+        entry = [self.labels[q] for q in self.queue]
         for u in (1, 2, 3):
-            kpre, dma = self.step(u, kpre, dma=dma)
+            kpre, vpre, dma = self.step(u, kpre, vpre, dma=dma)
         e("s_sub_u32 s67, s67, 1")
         e("s_cmp_eq_u32 s67, 0")
         e("s_cbranch_scc1 .Lfw64_drain_a_%=")
-        state_a = (list(self.queue), self.next_id)
+        state_a = (list(self.queue), vpre)
         for u in (4, 5, 6, 7):
-            kpre, dma = self.step(u, kpre, dma=dma)
+            kpre, vpre, dma = self.step(u, kpre, vpre, dma=dma)
         e("s_sub_u32 s67, s67, 1")
         e("s_cmp_eq_u32 s67, 0")
         e("s_cbranch_scc1 .Lfw64_drain_b_%=")
-        state_b = (list(self.queue), self.next_id)
-        kpre, dma = self.step(8, kpre, dma=dma)
-        assert len(self.queue) == len(entry_queue) == 3
+        state_b = (list(self.queue), vpre)
+        kpre, vpre, dma = self.step(8, kpre, vpre, dma=dma)
+        assert [self.labels[q] for q in self.queue] == entry and len(entry) == 9
         e("s_branch .Lfw64_loop_%=")
         e(".Lfw64_drain_a_%=:")
         self.queue = state_a[0]
-        self.drain(3)
+        self.drain(3, state_a[1])
         e(".Lfw64_drain_b_%=:")
         self.queue = state_b[0]
-        self.drain(7)
+        self.drain(7, state_b[1])
         self.out += self.cold
         e(".Lfw64_end_%=:")
         e("s_nop 15")      # the accumulators are read by compiler-generated code next

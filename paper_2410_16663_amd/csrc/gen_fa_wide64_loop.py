@@ -24,8 +24,9 @@ Register plan (per lane):
     v172           K fragment address (input);   v173 .. v180   V^T fragment address per 16-row block of O^T (v173 input)
     v181, v182     per-lane byte offsets of the K and V loads from global memory (inputs)
     v183 .. v186   per row block of a unit: the sum of its exponentials (fp16: the largest)
+    v187           causal limit of the lane's row in block 0, relative to the first key of its registers (input)
     v191, v192     temporaries;   v193 .. v200   per-lane offsets of the four loads per tensor
-Scalar registers s60 .. s67 are scratch of the block.
+Scalar registers s60 .. s71 are scratch of the block.
 
 A UNIT is 32 keys x the wave's 64 rows.  In step u the wave issues
     the 32 matrix instructions of unit u+1's logits   S(u+1) = K Q^T,
@@ -46,9 +47,29 @@ the matrix pipe and stops it: 33.0 with one behind each matrix instruction, whic
 So each matrix instruction is followed by at most one LDS read or load instruction and by as many vector instructions as
 are its even share of the step's, CAP cycles at least.
 
+Units that reach past the causal limit of the wave's first row are masked before their vector work, in blocks out of line too
+(two instructions per logit, 256 cycles): a wave walks its diagonal tile in the loop like the others.  (Its four waves' diagonal
+tiles lie one tile apart; done by compiler-scheduled code each of them holds the other waves up at a barrier.)
+
 LDS: four stages of (K tile, V tile); tile t lives in stage t % 4.  Barrier k (the k-th of the walk, the same count
 as in the compiler-scheduled loop around this block) publishes tile k+1 and certifies that no wave reads tile k-1
 any more; between barrier k and barrier k+1 every wave issues its share (four loads per tensor) of tile k+3.
+
+Nothing issues in line that can issue behind a matrix instruction: the next unit's first key, whether it has to be masked and
+whether it is the last are worked out there, and one branch a step, the one for the sums, stands for all three (counters and
+branches between the steps cost 1%).
+
+The reads ahead do not stop between steps: a step ends with reads of the next one's first fragments and begins with second
+products, whose V^T fragments need no barrier, while the first K fragments of a tile just published are on their way.  The
+barrier stands in an even step behind its last wait for V.  (Barrier and first K fragments between the steps, with the
+logits first, left the matrix pipe idle for the LDS latency once a tile: 1 x 32 x 131072 103.4 ms, now 101.6; 8 x 32 x
+8192 3776 us, 3742, fp16 3947, 3813; 512 queries on 32768 keys 250.5, 246.2.)
+
+Steps: the block computes S(0), runs step 0 (no second product yet), then the steady loop -- eight steps per pass,
+so that buffers and stages come round to where they started -- and leaves after step 2J-1 (J = number of tiles) through
+one of four exits, each followed by the second product of the last unit.  Up to there it requests tiles up to J+2, or again
+the last whole tile where there are no more, and reads K of tile J: what is not a tile of the walk goes to stages that nobody
+reads and to fragments that nobody uses.
 
 The reads ahead do not stop between steps: a step ends with reads of the next one's first fragments and begins with second
 products, whose V^T fragments need no barrier, while the first K fragments of a tile just published are on their way.  The
@@ -131,6 +152,7 @@ KADDR = "v172"
 VADDR = lambda db: f"v{173 + db}"
 KVOFF, VVOFF = "v181", "v182"
 SUM = lambda qb: f"v{183 + qb}"              # of a unit's exponentials (fp16: the largest)
+LIMIT = "v187"
 T4, T5 = "v191", "v192"
 DMAOFF = lambda tensor, n: f"v{193 + 4 * tensor + n}"     # per-lane byte offset of load n of a K / V tile
 
@@ -260,19 +282,34 @@ class Gen:
         L.append(f"v_cmp_nge_f32 vcc, 0x43800000, {T4}")             # not (256 >= sum): also true for inf and NaN
         return L
 
+    def mask_lines(self, b, first_key):
+        """Hides the logits of X[b] past each row's causal limit; first_key: the scalar register with the unit's first key.
+        Register mb, r of row block qb is key 16 mb + r of those the limit counts from."""
+        L = [f"v_subrev_u32 {T4}, {first_key}, {LIMIT}", f"v_mov_b32 {T5}, 0xff800000"]
+        for qb in range(QB):
+            for i in range(4 * MB):
+                L += [f"v_cmp_gt_i32 vcc, {16 * (i // 4) + i % 4 - 16 * qb}, {T4}",
+                      f"v_cndmask_b32 {x(b, qb, i)}, {x(b, qb, i)}, {T5}, vcc"]
+        return L
+
     def finish_sums(self, unit):
         """After the step's last matrix instruction: if the sum exceeded 256, a block out of line computes the row blocks'
-        logits again, moves the references up to the row maxima, rescales, and redoes the exponentials."""
+        logits again, moves the references up to the row maxima, rescales, and redoes the exponentials.  The same branch is
+        taken (s[64:65]) where the next unit has to be masked, which happens there too, and where there is none."""
         e = self.emit
         b = unit % 4
         k = self.nlabel
         self.nlabel += 1
-        e("s_and_b64 vcc, vcc, exec")
+        e("s_or_b64 vcc, vcc, s[64:65]")
         e(f"s_cbranch_vccnz .Lfw64_redo_{k}_%=")
         e(f".Lfw64_back_{k}_%=:")
         # ---- the block out of line
         main, self.out = self.out, []
         e(f".Lfw64_redo_{k}_%=:")
+        e(self.check_list()[-1])
+        e("s_and_b64 vcc, vcc, exec")
+        e("s_nop 3")
+        e(f"s_cbranch_vccz .Lfw64_next_{k}_%=")
         e("s_waitcnt lgkmcnt(0)")
         for f in range(MB * KB):
             e(self.k_text(unit, f, 3))               # (slot 3 is free between steps)
@@ -282,6 +319,12 @@ class Gen:
             e("s_nop 7")
         e("s_nop 15")
         e("s_nop 3")
+        e("s_sub_u32 s68, s66, 32")
+        e("s_cmp_lt_i32 s68, s70")
+        e(f"s_cbranch_scc1 .Lfw64_free_{k}_%=")
+        for ln in self.mask_lines(b, "s68"):
+            e(ln)
+        e(f".Lfw64_free_{k}_%=:")
         for qb in range(QB):
             e(f"v_max3_f32 {T4}, {x(b, qb, 0)}, {x(b, qb, 1)}, {x(b, qb, 2)}")
             for i in (3, 5):
@@ -318,14 +361,23 @@ class Gen:
             for ln in self.softmax_list(b, qb):
                 e(ln)
                 e("s_nop 0")       # (a result of v_exp is read two or more instructions later)
-        e("s_nop 7")               # (the fragments read ahead have landed: the main path's waits find fewer reads in flight)
+        # (the fragments read ahead have landed: the main path's waits find fewer reads in flight)
+        e(f".Lfw64_next_{k}_%=:")
+        if unit & 1:
+            e("s_cmp_ge_i32 s66, s67")
+            e(f"s_cbranch_scc1 .Lfw64_drain_{unit % 8}_%=")
+        e("s_nop 15")
+        e("s_cmp_lt_i32 s66, s70")
+        e(f"s_cbranch_scc1 .Lfw64_back_{k}_%=")
+        for ln in self.mask_lines((unit + 1) % 4, "s66"):
+            e(ln)
         e(f"s_branch .Lfw64_back_{k}_%=")
         self.cold += self.out
         self.out = main
 
     def dma_list(self, tile):
-        """This wave's share of the loads of a tile, then the advance of the two tile pointers s[60:61] / s[62:63], to be
-        spread over a step.  (Between m0's new value and the load that reads it something else has to issue.)"""
+        """This wave's share of the loads of a tile, then the advance of the two tile pointers s[60:61] / s[62:63] as long
+        as there are whole tiles (s69: how many), to be spread over a step.  (Between m0's new value and the load that reads it something else has to issue.)"""
         st = tile % NSTAGE
         G = []
         for tensor in (0, 1):
@@ -336,7 +388,8 @@ class Gen:
                 else:
                     G.append(f"s_add_u32 m0, %[ldsv], {st * TILEB + NW * n * 1024}")
                 G.append(f"global_load_lds_dwordx4 {DMAOFF(tensor, n)}, {ptr} offset:0")
-        G += [f"s_add_u32 s60, s60, {TILEB}", "s_addc_u32 s61, s61, 0", f"s_add_u32 s62, s62, {TILEB}", "s_addc_u32 s63, s63, 0"]
+        G += ["s_sub_u32 s69, s69, 1", "s_cmp_ge_i32 s69, 0", f"s_cselect_b32 s68, {TILEB}, 0"]
+        G += ["s_add_u32 s60, s60, s68", "s_addc_u32 s61, s61, 0", "s_add_u32 s62, s62, s68", "s_addc_u32 s63, s63, 0"]
         return G
 
     @staticmethod
@@ -371,7 +424,8 @@ class Gen:
         with_pv = u > 0
         valu = (self.pending_sums() if u > 0 else []) + self.softmax_all(u % 4) + self.check_list()
         self.check_distances(valu)
-        dma = list(dma)
+        # then the next unit's first key and whether it has to be masked or is none (all of these change the carry bit: one order)
+        dma = list(dma) + ["s_add_u32 s66, s66, 32", "s_cmp_ge_i32 s66, s71", "s_cselect_b64 s[64:65], -1, 0"]
         xq, xp = (u + 1) % 4, (u - 1) % 4
         nf = MB * KB                             # fragments of a unit's logits; as many of its second product
         assert nf == DB == 8
@@ -486,7 +540,11 @@ class Gen:
                 e(f"v_add_u32 {DMAOFF(tensor, n)}, {n * NW * 1024}, {KVOFF if tensor == 0 else VVOFF}")
         e("s_mov_b64 s[60:61], %[kptr]")
         e("s_mov_b64 s[62:63], %[vptr]")
-        e("s_mov_b32 s67, %[npairs]")
+        e("s_lshl_b32 s67, %[ntiles], 6")
+        e("s_mov_b32 s69, %[nadvance]")
+        e("s_mov_b32 s70, %[maskfrom]")
+        e("s_mov_b32 s66, 0")
+        e("s_min_i32 s71, s70, s67")
         for r in list(range(128)) + list(range(192, 208)):
             e(f"v_accvgpr_write_b32 a{r}, 0")
         for r in range(168, 172):
@@ -508,30 +566,25 @@ class Gen:
                 ids.append(self.k_read(0, f + 3))
         kpre = [self.k_read(1, f) for f in range(3)]
         e("s_nop 15")                               # the first step's vector work reads these logits
+        e("s_cmp_lt_i32 s66, s70")
+        e("s_cbranch_scc1 .Lfw64_first_%=")
+        for ln in self.mask_lines(0, "s66"):
+            e(ln)
+        e(".Lfw64_first_%=:")
         kpre, vpre, dma = self.step(0, kpre, [])
         e(".Lfw64_loop_%=:")
         entry = [self.labels[q] for q in self.queue]
-        for u in (1, 2, 3):
+        state = {}
+        for u in range(1, 9):
             kpre, vpre, dma = self.step(u, kpre, vpre, dma=dma)
-        e("s_sub_u32 s67, s67, 1")
-        e("s_cmp_eq_u32 s67, 0")
-        e("s_cbranch_scc1 .Lfw64_drain_a_%=")
-        state_a = (list(self.queue), vpre)
-        for u in (4, 5, 6, 7):
-            kpre, vpre, dma = self.step(u, kpre, vpre, dma=dma)
-        e("s_sub_u32 s67, s67, 1")
-        e("s_cmp_eq_u32 s67, 0")
-        e("s_cbranch_scc1 .Lfw64_drain_b_%=")
-        state_b = (list(self.queue), vpre)
-        kpre, vpre, dma = self.step(8, kpre, vpre, dma=dma)
+            if u & 1:
+                state[u] = (list(self.queue), vpre)
         assert [self.labels[q] for q in self.queue] == entry and len(entry) == 9
         e("s_branch .Lfw64_loop_%=")
-        e(".Lfw64_drain_a_%=:")
-        self.queue = state_a[0]
-        self.drain(3, state_a[1])
-        e(".Lfw64_drain_b_%=:")
-        self.queue = state_b[0]
-        self.drain(7, state_b[1])
+        for u in state:
+            e(f".Lfw64_drain_{u}_%=:")
+            self.queue, vpre = state[u]
+            self.drain(u, vpre)
         self.out += self.cold
         e(".Lfw64_end_%=:")
         e("s_nop 15")      # the accumulators are read by compiler-generated code next
@@ -539,8 +592,8 @@ class Gen:
         return "\n".join(self.out)
 
 
-CLOBBER_V = list(range(0, 160)) + list(range(168, 172)) + list(range(174, 181)) + list(range(183, 201))
-CLOBBER_S = list(range(60, 68))
+CLOBBER_V = list(range(0, 160)) + list(range(168, 172)) + list(range(174, 181)) + list(range(183, 187)) + list(range(188, 201))
+CLOBBER_S = list(range(60, 72))
 
 
 def generate(path):

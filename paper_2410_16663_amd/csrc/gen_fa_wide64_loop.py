@@ -182,12 +182,13 @@ class Gen:
 
     def wait_for(self, rid):
         if rid not in self.queue:
-            return
+            return False
         i = self.queue.index(rid)
         n_after = len(self.queue) - 1 - i
         assert n_after <= 15
         self.emit(f"s_waitcnt lgkmcnt({n_after})")
         self.queue = self.queue[i + 1:]
+        return True
 
     # fragment f of a unit's logits: key block f % MB, k-step f / MB
     def k_text(self, unit, f, slot):
@@ -456,7 +457,7 @@ class Gen:
         for si, (kind, i) in enumerate(slots):
             for n in range(QB):
                 qb = QB - 1 - n if si & 1 else n
-                if n == 0 and i != "ones":
+                if n == 0 and si == 0 and i != "ones":
                     self.wait_for(kids[i] if kind == "qk" else vids[i])
                 if kind == "qk":
                     e(self.qk(xq, qb, i, i % 4))
@@ -486,6 +487,11 @@ class Gen:
                     free = False
                 else:
                     free = True
+                if n == QB - 1 and si + 1 < len(slots):
+                    # the next fragment is waited for here, where the wait costs nothing if the fragment has arrived
+                    assert free
+                    k2, i2 = slots[si + 1]
+                    free = i2 == "ones" or not self.wait_for(kids[i2] if k2 == "qk" else vids[i2])
                 if free and dma:
                     e(dma.pop(0))
                 sub += 1

@@ -301,7 +301,6 @@ class Gen:
         b = unit % 4
         k = self.nlabel
         self.nlabel += 1
-        e("s_or_b64 vcc, vcc, s[64:65]")
         e(f"s_cbranch_vccnz .Lfw64_redo_{k}_%=")
         e(f".Lfw64_back_{k}_%=:")
         # ---- the block out of line
@@ -446,14 +445,6 @@ class Gen:
         done_cost = 0
         vi = 0
 
-        def publish():
-            """Even steps: tile u/2+1 is published (this wave's share has landed: all loads but the newest tile's)."""
-            if u & 1 == 0:
-                if with_pv:
-                    self.wait_for(vids[nf - 1])
-                e(f"s_waitcnt vmcnt({2 * NI})")
-                e("s_barrier")
-
         for si, (kind, i) in enumerate(slots):
             for n in range(QB):
                 qb = QB - 1 - n if si & 1 else n
@@ -485,6 +476,11 @@ class Gen:
                         else:
                             next_v.append(rid)
                     free = False
+                elif kind == "pv" and i == 6 and n == 0 and not u & 1:
+                    free = not self.wait_for(vids[nf - 1])            # V of unit u-1 has been read
+                elif kind == "qk" and i == 6 and n == 0 and with_pv and not u & 1:
+                    e("s_barrier")
+                    free = False
                 else:
                     free = True
                 if n == QB - 1 and si + 1 < len(slots):
@@ -492,26 +488,33 @@ class Gen:
                     assert free
                     k2, i2 = slots[si + 1]
                     free = i2 == "ones" or not self.wait_for(kids[i2] if k2 == "qk" else vids[i2])
+                    if kind == "pv" and i == 6 and not u & 1:
+                        # tile u/2+1 is published next: this wave's share has landed, all loads but the newest tile's
+                        assert free and not dma
+                        e(f"s_waitcnt vmcnt({2 * NI})")
+                if sub == nsub - 1:
+                    assert free and not dma and vi == len(valu)
+                    e("s_or_b64 vcc, vcc, s[64:65]")
+                    free = False
                 if free and dma:
                     e(dma.pop(0))
                 sub += 1
                 used = 0
-                goal = total * sub / nsub
+                goal = total * sub / (nsub - 2)      # (the outcome of the check is read behind the last one)
                 while vi < len(valu):
                     c = self.cost(valu[vi])
-                    if sub < nsub and used + c > CAP and done_cost + c / 2 > goal:
+                    if sub < nsub - 2 and used + c > CAP and done_cost + c / 2 > goal:
                         break
                     e(valu[vi])
                     done_cost += c
                     used += c
                     vi += 1
-            if kind == "pv" and i == 6:
-                publish()
         assert vi == len(valu) and not dma
         if not with_pv:
             # the reads ahead, in the order of the other steps
             next_v = [self.v_read(u, 0), self.v_read(u, 1)]
-            publish()
+            e(f"s_waitcnt vmcnt({2 * NI})")
+            e("s_barrier")
             next_k = [self.k_read(u + 2, f) for f in range(3)]
             next_v.append(self.v_read(u, 2))
         self.finish_sums(u)

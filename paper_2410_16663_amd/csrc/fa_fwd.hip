@@ -273,11 +273,13 @@ bool use_streaming_decode(const Options &opt, int Nq) { return Nq == 1 && opt[FA
 // fa_set_option(FA_OPT_FWD_MODE, ...) overrides.
 struct Decomposition {
     int mode, rows;
-    bool two_sums = false;       // fp16 on eight waves: both row sums (the four-wave kernels always carry both)
+    bool two_sums = false;       // fp16 on 256 rows or in two groups: both row sums (the four-wave kernels on 128 rows always carry both)
+    bool rows64 = false;         // FA_MODE_WIDE on waves of 64 rows: the kernel of FA_MODE_WIDE64
 };
 Decomposition choose_form(int forced, int B, int H, int Nq, int Nk, int D, int causal, int dtype) {
     const Decomposition split = {FA_MODE_SPLIT, 128}, wide = {FA_MODE_WIDE, 256}, four = {FA_MODE_WIDE, 128},
-                        fold = {FA_MODE_WIDE_FOLD, 256}, wide64 = {FA_MODE_WIDE64, 256};
+                        fold = {FA_MODE_WIDE_FOLD, 256}, wide64 = {FA_MODE_WIDE64, 256},
+                        wide_rows64 = {FA_MODE_WIDE, 256, false, true};
     const long long heads = (long long)B * H, blocks = heads * (((long long)Nq + 127) / 128);
     const bool four_fits = blocks < (1ll << 28);                // list positions and their multiples by 8 stay inside int
     if (forced == FA_MODE_SPLIT) return split;
@@ -293,7 +295,7 @@ Decomposition choose_form(int forced, int B, int H, int Nq, int Nk, int D, int c
         const int short_walk = dtype == FA_DTYPE_F16 ? 500 : D == 64 ? 350 : 460;   // (fp16's two sums cost the split form more)
         return Nk <= short_walk ? four : split;
     }
-    if (!four_fits) return D == 128 && avg_keys >= 4096 ? wide64 : wide;
+    if (!four_fits) return D == 64 ? wide : avg_keys >= 4096 ? wide64 : wide_rows64;
     if (D == 64) {
         if (W >= 256 && Nq > 128 && Nq <= 144 && (!causal || Nk >= Nq + 16)) return wide;
         if (!causal && avg_keys >= 1000 && W > 256 && W <= 404) return split;
@@ -312,13 +314,17 @@ Decomposition choose_form(int forced, int B, int H, int Nq, int Nk, int D, int c
         }
         return avg_keys > 4096 ? wide : four;
     }
-    if (causal && avg_keys >= 8192 && full_rounds && (nqt >= 16 || 100ll * Nq >= 93ll * 256 * nqt)) return wide64;
+    if (causal && full_rounds) {
+        if (avg_keys >= 8192 && (nqt >= 16 || 100ll * Nq >= 93ll * 256 * nqt)) return wide64;
+        const bool even = 4ll * avg_keys >= 3ll * Nk && Nk % 64 == 0;      // no block much longer than the others
+        if (avg_keys >= 2400 && even) return avg_keys >= 4096 ? wide64 : wide_rows64;
+    }
     if (causal && nqt >= 4) {
         if (W >= 256 && W <= 1024 && full_rounds && Nq <= 4096) return W <= 256 || avg_keys >= 8192 ? fold : Decomposition{FA_MODE_WIDE_FOLD, 128};
         if (Nq > 4096 ? blocks <= 576 : Nq >= 2048 && W < 640) return split;
     }
     if (avg_keys >= 4096 && (full_rounds || W >= 6 * 256)) return wide64;
-    if (!causal && Nk >= 1536 && (W <= 256 || full_rounds || W >= 6 * 256)) return wide;
+    if (!causal && Nk >= (Nk % 64 != 0 ? 2048 : W <= 256 ? 960 : 1216) && (W <= 256 || full_rounds || W >= 6 * 256)) return wide_rows64;
     return four;
 }
 
@@ -343,6 +349,8 @@ bool fp16_two_sums(int B, int H, int Nq, int Nk, int D, int causal) {
 Decomposition choose_mode(const Options &opt, int B, int H, int Nq, int Nk, int D, int causal, int dtype) {
     Decomposition d = choose_form(opt[FA_OPT_FWD_MODE], B, H, Nq, Nk, D, causal, dtype);
     d.two_sums = opt[FA_OPT_FWD_MODE] == FA_AUTO && fp16_two_sums(B, H, Nq, Nk, D, causal);
+    // (walks over 4096 keys have always been on WIDE64 with the one sum)
+    if ((d.mode == FA_MODE_WIDE64 || d.rows64) && (causal ? (long long)Nk - Nq / 2 : (long long)Nk) >= 4096) d.two_sums = false;
     return d;
 }
 
@@ -515,17 +523,21 @@ hipError_t launch_attention(const FaParams &p, Decomposition dec, int D, int cau
         if (!causal) f.off = p.Nk - 1;             // the causal instantiation with the diagonal past every key
         return dtype == FA_DTYPE_F16 ? launch<0, 64, true, true, 4, true>(f, grid, st) : launch<1, 64, true, true, 4>(f, grid, st);
     }
-    if (dtype == FA_DTYPE_F16 && dec.two_sums && mode != FA_MODE_WIDE64) {
+    if (dtype == FA_DTYPE_F16 && dec.two_sums && mode != FA_MODE_WIDE64 && !dec.rows64) {
         // (full attention through the causal instantiations, with the diagonal past every key)
         FaParams f = p;
         if (!causal) f.off = p.Nk - 1;
         if (mode == FA_MODE_SPLIT) return D == 64 ? launch<0, 64, true, false, 8, true>(f, grid, st) : launch<0, 128, true, false, 8, true>(f, grid, st);
-        if (mode == FA_MODE_WIDE) return D == 64 ? launch<0, 64, true, true, 8, true>(f, grid, st) : launch<0, 128, true, true, 8, true>(f, grid, st);
+        if (mode == FA_MODE_WIDE && D == 64) return launch<0, 64, true, true, 8, true>(f, grid, st);
         if (causal && D == 64) return launch_pair<0, 64, true>(p, grid, st);
     }
-    if (mode == FA_MODE_WIDE64) {
+    if (mode == FA_MODE_WIDE64 || dec.rows64) {
         if (D != 128) return hipErrorInvalidValue;
-        if (dtype == 0 && causal) hipLaunchKernelGGL((fa_fwd_wide64_kernel<0, true>), dim3(grid), dim3(256), 0, st, p);
+        if (dtype == 0 && dec.two_sums) {
+            FaParams f = p;
+            if (!causal) f.off = p.Nk - 1;         // the causal instantiation with the diagonal past every key
+            hipLaunchKernelGGL((fa_fwd_wide64_kernel<0, true, false, true>), dim3(grid), dim3(256), 0, st, f);
+        } else if (dtype == 0 && causal) hipLaunchKernelGGL((fa_fwd_wide64_kernel<0, true>), dim3(grid), dim3(256), 0, st, p);
         else if (dtype == 0) hipLaunchKernelGGL((fa_fwd_wide64_kernel<0, false>), dim3(grid), dim3(256), 0, st, p);
         else if (causal) hipLaunchKernelGGL((fa_fwd_wide64_kernel<1, true>), dim3(grid), dim3(256), 0, st, p);
         else hipLaunchKernelGGL((fa_fwd_wide64_kernel<1, false>), dim3(grid), dim3(256), 0, st, p);
@@ -697,13 +709,13 @@ int fa_fwd_plan(int B, int H, int Nq, int Nk, int D, int causal, int dtype, fa_p
     plan->mode = mode;
     plan->block_m = BM;
     plan->block_n = BN;
-    plan->threads = mode == FA_MODE_WIDE64 || four ? 256 : 512;
+    plan->threads = mode == FA_MODE_WIDE64 || dec.rows64 || four ? 256 : 512;
     plan->grid = four && D == 128 ? rows_grid((long long)B * H, nqt) : (int)(((nwork + 7) / 8) * 8);
     plan->work_items = nwork;
     plan->tiles_visited = visited * B * H;
     plan->tiles_total = nwork * tiles_k;
     plan->lds_bytes = (mode == FA_MODE_WIDE || four ? 1 : 2) * 4 * BN * D * 2;    // sets of 2+2 tiles
-    if (mode == FA_MODE_WIDE64) plan->lds_bytes = 4 * (16 * 1088 + BN * D * 2);   // ring of four (padded K tile, V tile)
+    if (mode == FA_MODE_WIDE64 || dec.rows64) plan->lds_bytes = 4 * (16 * 1088 + BN * D * 2);   // ring of four (padded K tile, V tile)
     return FA_OK;
 }
 

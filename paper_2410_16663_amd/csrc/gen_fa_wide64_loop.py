@@ -1,6 +1,6 @@
 #!/usr/bin/env python3
 """Writes fa_attention_wide64_loop.inc: the check-free main loop of fa_fwd_wide64_kernel as one inline-assembly
-block per storage type -- the software-pipelined form of the attention loop for waves of 64 query rows (four 16-row
+block per storage type and number of row sums -- the software-pipelined form of the attention loop for waves of 64 query rows (four 16-row
 blocks qb = 0 .. 3 that share every K and V fragment read from LDS).  One wave per SIMD, the whole register file.
 
 Why assembly, and why generated: with one wave per SIMD nothing hides a wave's vector work but the wave itself, so
@@ -19,11 +19,11 @@ Register plan (per lane):
                    as logits (key block mb in registers 4*mb .. +3), then (overwritten in place) as packed exponentials
                    P = its first 4 registers
     v128 .. v143   four K fragments in flight;   v144 .. v159   four V^T fragments in flight
-    v160+qb m_ref, v164+qb l_run (bf16: sum of the unrounded exponentials)    (outputs)
+    v160+qb m_ref, v164+qb l_run (two sums: of the unrounded exponentials)    (outputs)
     v168 .. v171   the fragment of ones
     v172           K fragment address (input);   v173 .. v180   V^T fragment address per 16-row block of O^T (v173 input)
     v181, v182     per-lane byte offsets of the K and V loads from global memory (inputs)
-    v183 .. v186   per row block of a unit: the sum of its exponentials (fp16: the largest)
+    v183 .. v186   per row block of a unit: the sum of its exponentials (one sum: the largest)
     v187           causal limit of the lane's row in block 0, relative to the first key of its registers (input)
     v191, v192     temporaries;   v193 .. v200   per-lane offsets of the four loads per tensor
 Scalar registers s60 .. s71 are scratch of the block.
@@ -151,15 +151,16 @@ ONES = "v[168:171]"
 KADDR = "v172"
 VADDR = lambda db: f"v{173 + db}"
 KVOFF, VVOFF = "v181", "v182"
-SUM = lambda qb: f"v{183 + qb}"              # of a unit's exponentials (fp16: the largest)
+SUM = lambda qb: f"v{183 + qb}"              # of a unit's exponentials (one sum: the largest)
 LIMIT = "v187"
 T4, T5 = "v191", "v192"
 DMAOFF = lambda tensor, n: f"v{193 + 4 * tensor + n}"     # per-lane byte offset of load n of a K / V tile
 
 
 class Gen:
-    def __init__(self, bf16):
+    def __init__(self, bf16, two_sums):
         self.bf16 = bf16
+        self.two_sums = two_sums
         self.mfma = "v_mfma_f32_16x16x32_bf16" if bf16 else "v_mfma_f32_16x16x32_f16"
         self.cvt = "v_cvt_pk_bf16_f32" if bf16 else "v_cvt_pk_f16_f32"
         self.out = []
@@ -223,7 +224,7 @@ class Gen:
     # ---- the vector work of one unit and row block, as a list of instructions (buffer b)
     def softmax_list(self, b, qb):
         """In place: logits X[b][qb] -> exponentials against the current reference, packed as P[b][qb]; leaves in SUM the sum
-        of the exponentials (fp16: the largest).  The exponentials of the second group of four elements alternate with the
+        of the exponentials (one sum: the largest).  The exponentials of the second group of four elements alternate with the
         additions / conversions of the first."""
         L = []
         acc = SUM(qb)
@@ -233,7 +234,7 @@ class Gen:
             for pr in (2 * g, 2 * g + 1):          # pair pr = elements 2pr, 2pr+1 -> register pr
                 a, bb = x(b, qb, 2 * pr), x(b, qb, 2 * pr + 1)
                 one = []
-                if self.bf16:
+                if self.two_sums:
                     if pr == 0:
                         one.append(f"v_add_f32 {acc}, {a}, {bb}")
                     else:
@@ -271,12 +272,12 @@ class Gen:
     def pending_sums(self):
         """Adds the previous unit's sums (left in the temporaries by its vector work) to the running sums: the first
         vector instructions of the next step, or of the drain."""
-        return [f"v_add_f32 {L_RUN(qb)}, {L_RUN(qb)}, {SUM(qb)}" for qb in range(QB)] if self.bf16 else []
+        return [f"v_add_f32 {L_RUN(qb)}, {L_RUN(qb)}, {SUM(qb)}" for qb in range(QB)] if self.two_sums else []
 
     def check_list(self):
-        """The test "the sum over all row blocks <= 256" (fp16: the largest), which proves that no exponential exceeded 256,
+        """The test "the sum over all row blocks <= 256" (one sum: the largest), which proves that no exponential exceeded 256,
         leaving the outcome in vcc: the last vector instructions of a step."""
-        if self.bf16:
+        if self.two_sums:
             L = [f"v_add_f32 {T4}, {SUM(0)}, {SUM(1)}", f"v_add_f32 {T5}, {SUM(2)}, {SUM(3)}", f"v_add_f32 {T4}, {T4}, {T5}"]
         else:
             L = [f"v_max_f32 {T4}, {SUM(0)}, {SUM(1)}", f"v_max3_f32 {T4}, {T4}, {SUM(2)}, {SUM(3)}"]
@@ -325,11 +326,20 @@ class Gen:
         for ln in self.mask_lines(b, "s68"):
             e(ln)
         e(f".Lfw64_free_{k}_%=:")
+        if unit == 0:
+            # the walk's first reference is the maximum over the whole first tile, as in the other kernels: the key that sets it
+            # has a probability of 1, without rounding (over 32 keys the results are 0.1 to 0.2% further from 64 bits)
+            e("s_cmp_lt_i32 s66, s70")
+            e(f"s_cbranch_scc1 .Lfw64_tile_{k}_%=")
+            for ln in self.mask_lines(1, "s66"):
+                e(ln)
+            e(f".Lfw64_tile_{k}_%=:")
         for qb in range(QB):
-            e(f"v_max3_f32 {T4}, {x(b, qb, 0)}, {x(b, qb, 1)}, {x(b, qb, 2)}")
-            for i in (3, 5):
-                e(f"v_max3_f32 {T4}, {T4}, {x(b, qb, i)}, {x(b, qb, i + 1)}")
-            e(f"v_max_f32 {T4}, {T4}, {x(b, qb, 7)}")
+            X8 = [x(b, qb, i) for i in range(8)] + ([x(1, qb, i) for i in range(8)] if unit == 0 else [])
+            e(f"v_max3_f32 {T4}, {X8[0]}, {X8[1]}, {X8[2]}")
+            for i in range(3, len(X8) - 1, 2):
+                e(f"v_max3_f32 {T4}, {T4}, {X8[i]}, {X8[i + 1]}")
+            e(f"v_max_f32 {T4}, {T4}, {X8[-1]}")
             for swap in ("v_permlane32_swap_b32_e32", "v_permlane16_swap_b32_e32"):   # the lane groups hold different keys of one query
                 e(f"v_mov_b32 {T5}, {T4}")
                 e("s_nop 1")
@@ -343,7 +353,7 @@ class Gen:
             e(f"v_cndmask_b32 {M_REF(qb)}, {M_REF(qb)}, {T4}, vcc")
             e("s_nop 1")
             e(f"v_cndmask_b32 {T5}, 1.0, {T5}, vcc")
-            if self.bf16:
+            if self.two_sums:
                 e(f"v_mul_f32 {L_RUN(qb)}, {T5}, {L_RUN(qb)}")
             # the accumulators live in AGPRs: out, times alpha, back in -- four at a time through the K fragment
             # registers of slot 3 (free here); the second products issued earlier in this step have long retired
@@ -610,9 +620,10 @@ def generate(path):
     parts = ["// GENERATED by gen_fa_wide64_loop.py -- do not edit; change the script and build again.",
              "// The software-pipelined check-free main loop of fa_fwd_wide64_kernel as inline assembly with hand-chosen",
              "// registers and instruction order (plan and reasons are in the script's header).  A fragment of fa_fwd.hip.", ""]
-    for name, bf16 in (("FA_WIDE64_LOOP_ASM_F16", False), ("FA_WIDE64_LOOP_ASM_BF16", True)):
+    for name, bf16, two_sums in (("FA_WIDE64_LOOP_ASM_F16", False, False), ("FA_WIDE64_LOOP_ASM_F16_TWO_SUMS", False, True),
+                                 ("FA_WIDE64_LOOP_ASM_BF16", True, True)):
         parts.append(f"#define {name} \\")
-        lines = Gen(bf16).block().split("\n")
+        lines = Gen(bf16, two_sums).block().split("\n")
         parts.append(" \\\n".join('    "' + ln + '\\n\\t"' for ln in lines))
         parts.append("")
     clob = ", ".join([f'"v{r}"' for r in CLOBBER_V] + [f'"s{r}"' for r in CLOBBER_S] + ['"vcc"', '"scc"', '"m0"', '"memory"'])

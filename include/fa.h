@@ -72,26 +72,29 @@ int fa_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
  * Work decomposition fa_fwd uses for a problem (section 4.1: tiles above the diagonal are
  * skipped; appendix A: the work is split over the sequence as well as over batch and heads).
  * FA_MODE_SPLIT: a workgroup owns 128 query rows and its two wave groups take alternate
- * 64-key tiles; FA_MODE_WIDE: all waves of a workgroup walk the same tiles, eight waves on 256 query rows or four on 128
+ * 64-key tiles; FA_MODE_WIDE: all waves of a workgroup walk the same tiles, eight waves on 256 query rows, at D = 128 four
+ * of 64 rows each (the kernel of FA_MODE_WIDE64; fa_plan_t.threads is 256), or four on 128
  * (fa_plan_t.block_m says which; four-wave workgroups at D = 128 are launched once and take block of rows after block of
  * rows, heavy and light causal ones in turn); FA_MODE_WIDE_FOLD (causal only): WIDE with every workgroup's work balanced --
  * on 256 rows, each workgroup's eight 32-row blocks are taken four from the cheap end of the sequence and four, mirrored,
  * from the expensive end, and once the cheap blocks are done their waves take every other tile of the expensive ones; on 128
  * rows, the order of the four-wave workgroups' blocks does it.
  * FA_MODE_WIDE64 (D = 128 only): 256 query rows per workgroup as in WIDE, but as four waves of 64
- * rows, one per SIMD, so that every K and V fragment read from LDS feeds two matrix instructions,
+ * rows, one per SIMD, so that every K and V fragment read from LDS feeds twice as many matrix instructions,
  * with a software-pipelined main loop (the softmax of one 32-key unit issued between the matrix
  * instructions of its neighbours).
  * With W = B*H*ceil(Nq/256) and rounds of 256 workgroups, fa_fwd picks SPLIT for at most 256 blocks of 128 rows unless the
  * walk is short (bf16: Nk <= 460, at D = 64 350; fp16: 500), then WIDE on 128 rows.  Beyond that, at D = 128: SPLIT for causal
  * problems over Nq = 2048 with W < 640 (Nq <= 4096) or of at most 576 such blocks (longer) that are not FOLD's; WIDE_FOLD for
  * causal problems with 768 < Nq <= 4096 whose one to four rounds fill the last to 85%; WIDE64 where a query sees 4096 keys or
- * more on average (Nk, or Nk - Nq/2 when causal) and its rounds are filled or many (from 8192 keys before FOLD).  At D = 64:
+ * more on average (Nk, or Nk - Nq/2 when causal) and its rounds are filled or many (from 8192 keys before FOLD); WIDE on its
+ * kernel in filled rounds from 2400 keys on average (causal, before FOLD, no block of rows much longer than the others) or
+ * 960 to 1216 keys (full; 2048 where Nk is no multiple of 64, from 1536 on eight waves if rounds are not filled).  At D = 64:
  * WIDE_FOLD for causal triangles (Nk little over Nq) of up to four rounds whose last one is not nearly empty and for blocks
  * of rows on long caches of 1.65 to two rounds; SPLIT for triangles of 1 to 1.5 rounds or little over two, for such blocks of
  * rows below 1.65 rounds, for other triangles over 2200 keys on average in up to 7.4 rounds, and for full attention over 1000
  * keys and more in 1 to 1.6 rounds, over 1535 in 2 to 2.5 (below 3000 only if the rounds of 128-row blocks are filled).  Else
- * WIDE, on 256 rows for long walks (full: 1536 keys, at D = 64 in bf16 850; causal at D = 64: over 4096) and on 128 otherwise.
+ * WIDE, on 256 rows for long walks at D = 64 (full: 1536 keys, in bf16 850; causal: over 4096) and on 128 otherwise.
  * fa_set_option(FA_OPT_FWD_MODE, ...) overrides the choice (tests, tuning).
  * Nq = 1 (one decoding step) takes none of these: FA_MODE_STREAM, the register-streaming kernel
  * described at fa_fwd_splitkv, one workgroup per (batch, head) -- full speed when B*H fills the

@@ -238,7 +238,7 @@ bool use_streaming_decode(const Options &opt, int Nq) { return Nq == 1 && opt[FA
 //    500 1.00, 750 0.89).
 //  * whole rounds of causal work (one to four rounds of 256-row workgroups, the last one filled to 85%), D = 128:
 //    FA_MODE_WIDE_FOLD, whose workgroups all carry the same triangular work and whose finished waves help the others, for a
-//    single round (1 x 32 x 2048: 44, rows 47; several rounds: rows, 1 x 32 x 4096: 133 instead of 148).
+//    single round (1 x 32 x 2048: 40.5, rows 44.5; several rounds: rows, 1 x 32 x 4096: 130 instead of 153).
 //  * causal triangles at D = 64 (Nk little over Nq, Nq > 768) up to four rounds: FA_MODE_WIDE_FOLD as well (11 x 8365, 1.4
 //    rounds: fold 149, split 175, four 181, wide 239; 94 x 2048, 2.9 rounds: 69, 79, 85, 91; beyond four rounds the forms
 //    are within 5%, 204 x 2341 bf16: four 213, fold 227), but for a second or third round that would be nearly empty (16 x
@@ -250,9 +250,18 @@ bool use_streaming_decode(const Options &opt, int Nq) { return Nq == 1 && opt[FA
 //    to two (217 x 512 on 1969: 70, split 74, four 75); full attention likewise (169 x 321 on 3162: split 1.00, four 1.11,
 //    wide 1.48 of the best; 50 x 1878: 1.00, 1.01, 1.14; 32 x 3209, 1.62 rounds: 1.05, 1.07, 1.00).
 //  * long walks at D = 128 (4096 keys per query on average): FA_MODE_WIDE64, where its rounds of 256 are filled (1 x 20 x
-//    8192, two and a half rounds: 437, rows 329); from 8192 keys on before the fold (1 x 32 x 2048 on 16384: 440, fold 472;
-//    2 x 32 x 4096 on 12288 fp16: 1230, 1269; 1 x 32 x 2048 on 7168: 207, 202), unless the last of a few blocks is mostly
-//    padding, which the fold spreads over a head's workgroups (80 x 1302 on 16068 fp16: 1020, rows 1047, fold 939).
+//    8192, two and a half rounds: 437, rows 329), unless the last of a few blocks is mostly padding, which the fold spreads over
+//    a head's workgroups (80 x 1302 on 16068 fp16: 1020, rows 1047, fold 939).
+//  * the same kernel at D = 128 below 4096 keys (rows64; plans report FA_MODE_WIDE), where rounds are filled:
+//    - full attention from 960 keys in one round, 1216 in several, 2048 where the last tile is ragged (rows, rows64: 1 x 32 x 2048
+//      on 768 29.2, 29.3; on 1024 36.4, 35.0; on 1536 49.9, 46.4; on 2048 63.5, 58.1; on 2100 65.7, 66.3; 128 x 1024 on 1024 75.8,
+//      77.9; on 1280 89.5, 87.0; on 2048 134, 125; on 2100 137.6, 137.4; wide is behind both, and is left with less than a round
+//      on a ragged 1536 to 2047 keys);
+//    - causal blocks of rows on long caches, 2400 keys on average, where no block's walk is over 4/3 of the average, before the
+//      fold (fold, rows, rows64: 1 x 32 x 2048 on 3072 71.6, 72.1, 73.5; on 4096 107, 102, 97; on 6144 165, 154, 145; 64 x 2048
+//      on 4096 215, 195, 190; 128 x 1024 on 2048 122, 111, 116; on 3072 185, 174, 162).  Triangles stay on rows, where they are
+//      about level (3 x 32 x 4096 402, 400, the walks' first references closer to 64 bits), and so do uneven rounds (1 x 40 x
+//      2048 on 6144: 225, 239; full on 2048: 98.7, 100).
 //  * a second round of 512 256-row workgroups that would be nearly empty, full attention at D = 64 over 1535 keys: FA_MODE_SPLIT
 //    (wide and split: 9 x 2 x 8712, 2.46 times 256 of them, 436, 391; 13 x 5 x 1896, 2.03, 96, 77; 1 x 20 x 7058, 2.19, 344, 311;
 //    10 x 20 x 599 on 2673, 2.34, 112, 98), unless the last round of 256 128-row workgroups is as empty and the walk below 3000
@@ -262,9 +271,9 @@ bool use_streaming_decode(const Options &opt, int Nq) { return Nq == 1 && opt[FA
 //    640; 4 x 12 x 9280, 6.9, 631, 600; below against four waves: 3 x 12 x 7581 fp16, 4.2, 387, 370; 3 x 20 x 5446, 5.2, 301, 286; 2 x
 //    32 x 6731, 6.75, 486, 475; 6 x 20 x 4496, 8.4, level; 10 x 12 x 5019, 9.4, 520, 523).
 //  * everything else on four waves, whose waves share a SIMD with other workgroups' (D = 128 causal: 16 x 32 x 2048 590,
-//    wide 745; 3 x 20 x 1531 47, split 68, wide 70; full: 47 x 32 x 280 122, wide 205), but for full attention over 1536
-//    keys and more (at D = 64 in bf16 and filled rounds 850), where the tiles loaded per 256 rows count (4 x 32 x 2048: wide
-//    266, rows 273; D = 64, 8 x 32 x 4096: wide 1141, four 1184), and for causal walks over 4096 keys at D = 64.  129 .. 144
+//    wide 745; 3 x 20 x 1531 47, split 68, wide 70; full: 47 x 32 x 280 122, wide 205), but at D = 64 for full attention over
+//    1536 keys and more (in bf16 and filled rounds 850), where the tiles loaded per 256 rows count (8 x 32 x 4096: wide 1141,
+//    four 1184), and for causal walks over 4096 keys.  129 .. 144
 //    rows at D = 64 stay one workgroup (464 x 144 on 161: wide 11.5, four 14.6; 1452 x 133 full: 32, 35; equal for square
 //    causal ones).
 //  * FA_MODE_SPLIT besides for causal Nq >= 2048 below 2.5 rounds at D = 128, its place in fa_fwd_plan's documented answer
@@ -325,6 +334,7 @@ Decomposition choose_form(int forced, int B, int H, int Nq, int Nk, int D, int c
     }
     if (avg_keys >= 4096 && (full_rounds || W >= 6 * 256)) return wide64;
     if (!causal && Nk >= (Nk % 64 != 0 ? 2048 : W <= 256 ? 960 : 1216) && (W <= 256 || full_rounds || W >= 6 * 256)) return wide_rows64;
+    if (!causal && Nk >= 1536 && W <= 256 && !full_rounds) return wide;
     return four;
 }
 
@@ -528,7 +538,7 @@ hipError_t launch_attention(const FaParams &p, Decomposition dec, int D, int cau
         FaParams f = p;
         if (!causal) f.off = p.Nk - 1;
         if (mode == FA_MODE_SPLIT) return D == 64 ? launch<0, 64, true, false, 8, true>(f, grid, st) : launch<0, 128, true, false, 8, true>(f, grid, st);
-        if (mode == FA_MODE_WIDE && D == 64) return launch<0, 64, true, true, 8, true>(f, grid, st);
+        if (mode == FA_MODE_WIDE) return D == 64 ? launch<0, 64, true, true, 8, true>(f, grid, st) : launch<0, 128, true, true, 8, true>(f, grid, st);
         if (causal && D == 64) return launch_pair<0, 64, true>(p, grid, st);
     }
     if (mode == FA_MODE_WIDE64 || dec.rows64) {
@@ -566,7 +576,12 @@ hipError_t launch_attention(const FaParams &p, Decomposition dec, int D, int cau
     switch ((dtype << 2) | ((D == 128) << 1) | (causal ? 1 : 0)) {
         case 0: e = launch<0, 64, false, true>(p, grid, st); break;
         case 1: e = launch<0, 64, true, true>(p, grid, st); break;
-        case 2: e = launch<0, 128, false, true>(p, grid, st); break;
+        case 2: {                                  // (the causal instantiation with the diagonal past every key)
+            FaParams f = p;
+            f.off = p.Nk - 1;
+            e = launch<0, 128, true, true>(f, grid, st);
+            break;
+        }
         case 3: e = launch<0, 128, true, true>(p, grid, st); break;
         case 4: e = launch<1, 64, false, true>(p, grid, st); break;
         case 5: e = launch<1, 64, true, true>(p, grid, st); break;

@@ -141,7 +141,7 @@ int fa_fwd_plan(int B, int H, int Nq, int Nk, int D, int causal, int dtype, fa_p
  * own that streams K and V through registers (one multiply-add per element leaves the matrix
  * cores nothing to reuse) and keeps the probabilities in fp32; fa_set_option(FA_OPT_DECODE_KERNEL, 1)
  * sends it through the tile kernel instead (tests, tuning).  With several query blocks per head (a chunk
- * of a chunked prefill: Nq > 256) the call is bound by the matrix cores instead, and at D = 128 runs of 4096
+ * of a chunked prefill: Nq > 256) the call is bound by the matrix cores instead, and at D = 128 runs of 1400
  * keys or more go to the kernel of FA_MODE_WIDE64.
  *
  *   nsplit          : > 0: number of runs (clamped to the number of 64-key tiles, at most 1024);

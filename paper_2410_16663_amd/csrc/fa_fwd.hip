@@ -848,10 +848,12 @@ static int splitkv(const Options &opt, const void *q, const void *k, const void 
         }
         return FA_OK;
     }
-    // keys a query sees per run, on average (as in choose_mode): from 4096 the wide64 kernel is the faster one
+    // keys a query sees per run, on average (as in choose_mode): from 1400 the wide64 kernel is the faster one (us, tile kernel and
+    // it, keys per run: 32 x 300 on 3300, 787, 38.5, 40.6; 12 x 1000 on 4000, 700, 41.5, 45.8; 12 x 1000 on 7000, 1300, 59.7, 58.4;
+    // 32 x 512 on 6512, 1564, 78, 72; 32 x 300 on 6300, 1537, 62, 53; 32 x 1000 on 7000, 3250, 139, 114)
     const long long avg_keys = causal ? (long long)Nk - Nq / 2 : (long long)Nk;
     const bool long_runs = D == 128 && !p.kv_stream && opt[FA_OPT_FWD_MODE] != FA_MODE_WIDE &&
-                           avg_keys / pl.nsplit >= 4096;
+                           avg_keys / pl.nsplit >= 1400;
     const int key = (dtype << 2) | ((D == 128) << 1) | (causal ? 1 : 0);
     switch (key) {
         case 0: e = launch_splitkv<0, 64, false>(p, pl.grid_x, rows, long_runs, st); break;

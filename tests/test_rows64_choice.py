@@ -8,7 +8,7 @@ import pytest
 
 from paper_2410_16663_amd import binding as fa
 from paper_2410_16663_amd import inputs as I
-from gpu_util import check_against_oracle, run_fa_fwd
+from gpu_util import check_against_oracle, run_fa_fwd, run_fa_fwd_splitkv
 
 D = 128
 
@@ -42,3 +42,20 @@ def test_sampled_rows(oracle, B, H, Nq, Nk, causal, dtype):
     rows = np.unique(np.concatenate([rng.integers(0, B * H * Nq, 1000), [0, Nq - 1, B * H * Nq - 1]]))
     o_ref, lse_ref = oracle.attention_fwd(q, k, v, scale, causal, dtype, rows=rows)
     check_against_oracle(o.reshape(-1, D)[rows], lse.reshape(-1)[rows], o_ref, lse_ref, dtype, f"rows64 {(B, H, Nq, Nk)}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("H,Nq,Nk,nsplit,causal", [
+    (4, 300, 2950, 2, True), (3, 520, 4480, 3, True), (2, 257, 2801, 2, False), (2, 513, 3071, 2, True)])
+def test_runs_of_1400_keys_and_more(oracle, H, Nq, Nk, nsplit, causal, dtype):
+    """Split-KV runs of several query blocks on that kernel: runs that start and end anywhere, ragged last tiles."""
+    print(f"case rows64 runs {(H, Nq, Nk, nsplit, causal)} dtype={dtype}", flush=True)
+    assert (Nk - Nq // 2 if causal else Nk) // nsplit >= 1400
+    rng = np.random.default_rng(Nq + Nk + dtype)
+    q, k, v = (I.f32_to_bits(rng.standard_normal((1, H, n, D), dtype=np.float32), dtype) for n in (Nq, Nk, Nk))
+    scale = 1.0 / math.sqrt(D)
+    o, lse, plan = run_fa_fwd_splitkv(q, k, v, scale, causal, dtype, nsplit)
+    assert plan.nsplit == nsplit
+    o_ref, lse_ref = oracle.attention_fwd(q, k, v, scale, causal, dtype)
+    check_against_oracle(o, lse, o_ref, lse_ref, dtype, f"rows64 runs {(H, Nq, Nk, nsplit)}")
